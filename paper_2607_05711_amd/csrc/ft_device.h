@@ -228,6 +228,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
 }
 
+// 16-byte chunk swizzles of LDS tiles: 64-byte rows (4 chunks) and 128-byte
+// rows (8 chunks).
+__device__ __forceinline__ int swz64(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
+__device__ __forceinline__ int swz128(int r) { return (r & 7) ^ ((r >> 3) & 1); }
+
 // An offset no buffer here reaches: a load from it returns zeros.
 constexpr uint32_t kOobOffset = 0x80000000u;
 

@@ -36,6 +36,13 @@ hipError_t launch_gemm_fp4(bool bwd, const uint8_t* a, const uint8_t* as, const 
                            int M, int N, int K, const float* P, int R, const uint16_t* lr,
                            const uint16_t* bias, void* out, bool out_f32, hipStream_t st);
 
+// The same product on tm x 128 output tiles (tm = 64 or 128), any K and N that are
+// multiples of 32; whether its 32-bit offsets and LDS hold this shape.
+bool gemm_fp4_tile_supported(bool bwd, int M, int N, int K, int R, bool out_f32);
+hipError_t launch_gemm_fp4_tile(bool bwd, int tm, const uint8_t* a, const uint8_t* as, const uint8_t* wq,
+                                const uint8_t* ws, int M, int N, int K, const float* P, int R, const uint16_t* lr,
+                                const uint16_t* bias, void* out, bool out_f32, hipStream_t st);
+
 // Epilogues of the MLP pair (the output NO columns feed the next linear).
 enum { EPI_PLAIN = 0, EPI_GELU = 1, EPI_DGELU = 2 };
 struct GemmEpilogue {

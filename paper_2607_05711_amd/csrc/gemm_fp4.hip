@@ -27,6 +27,9 @@ constexpr int GROW = GK / 2;            // bytes of codes per tile row per stage
 constexpr int GSTRIDE = GROW + 16;      // padded LDS row stride (bytes)
 constexpr int GTILE = GB * GSTRIDE;     // bytes per operand tile per stage
 
+// Register-staged kernel with 64-bit addressing, for what the others do not
+// hold: operands of 2 GiB or more, and reductions whose scales do not fit LDS
+// (above some 50000 elements) that are no multiple of 128.
 template <bool BWD, bool OUT_F32>
 __global__ __launch_bounds__(256, 1) void k_gemm_fp4_generic(const uint8_t* __restrict__ A, const uint8_t* __restrict__ As,
                                                      const uint8_t* __restrict__ Wq, const uint8_t* __restrict__ Ws,
@@ -273,10 +276,6 @@ constexpr int LR_COLS = 32;              // up-projection columns per low-rank s
 // Stage kinds, and a compile-time tag for the pipeline bodies.
 enum { SK_NONE = 0, SK_FP4 = 1, SK_LR = 2 };
 template <int V> struct IC { static constexpr int value = V; };
-
-// 16-byte chunk swizzles: 64-byte rows (4 chunks) and 128-byte rows (8 chunks)
-__device__ __forceinline__ int swz64(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
-__device__ __forceinline__ int swz128(int r) { return (r & 7) ^ ((r >> 3) & 1); }
 
 // Workgroup id -> output tile.  Consecutive ids go to different XCDs, so each
 // XCD gets a contiguous range of tiles; within it tiles run in groups of 4
@@ -1217,16 +1216,42 @@ __global__ __launch_bounds__(256, 1) void k_gemm_fp4_pipe(const uint8_t* __restr
   }
 }
 
+static bool pipe_ok(bool bwd, int M, int N, int K, int R) {
+  // buffer ranges are 32-bit: the pipelined kernel takes operands below 2 GiB
+  const int NO = bwd ? K : N, KR = bwd ? N : K;
+  return KR % 128 == 0 && K % 128 == 0 && (size_t)M * KR / 2 < (1u << 31) && (size_t)N * K / 2 < (1u << 31) &&
+         (size_t)M * (R > 0 ? R : 1) * 4 < (1u << 31) && (size_t)M * NO * 2 < (1u << 31);
+}
+
 hipError_t launch_gemm_fp4(bool bwd, const uint8_t* a, const uint8_t* as, const uint8_t* wq, const uint8_t* ws,
                            int M, int N, int K, const float* P, int R, const uint16_t* lr,
                            const uint16_t* bias, void* out, bool out_f32, hipStream_t st) {
   const int NO = bwd ? K : N;
   const int KR = bwd ? N : K;
   const int tm = (M + GB - 1) / GB, tn = (NO + GB - 1) / GB;
-  // buffer ranges are 32-bit: the pipelined kernel takes operands below 2 GiB
-  const bool small = (size_t)M * KR / 2 < (1u << 31) && (size_t)N * K / 2 < (1u << 31) &&
-                     (size_t)M * (R > 0 ? R : 1) * 4 < (1u << 31) && (size_t)M * NO * 2 < (1u << 31);
-  if (KR % 128 == 0 && K % 128 == 0 && small) {
+  const bool pipe = pipe_ok(bwd, M, N, K, R);
+  if (gemm_fp4_tile_supported(bwd, M, N, K, R, out_f32)) {
+    // 256x256 tiles against tiles of 64x128 or 128x128, by estimated time:
+    // rounds of workgroups times the time of one workgroup, in units of 10 ns,
+    // fitted to back-to-back launches of all three (M = 100 to 4608, KR = 256
+    // to 12288).  With few 256x256 tiles most of the chip idles while one CU
+    // works through a whole reduction: 512 x 12288 -> 3072 (24 tiles, or 192
+    // of 64x128) 65 us against 31; 512 x 3072 -> 3072 22.5 against 12.3;
+    // 2048 x 3072 -> 3072 (96, or 384 of 128x128) 23.4 against 20.4.  With a
+    // round of them or more the larger tile's fewer LDS and L2 bytes per MFMA
+    // win: 4608 x 3072 -> 9216 83 us against 105 (128x128) and 136 (64x128).
+    const long nst = (KR + 255) / 256, nlr = (R + 31) / 32;
+    auto tiles = [&](int h, int w) { return (long)((M + h - 1) / h) * ((NO + w - 1) / w); };
+    auto rounds = [](long t, long per) { return (t + per - 1) / per; };
+    const long t64 = tiles(64, 128), t128 = tiles(128, 128);
+    const long c256 = rounds(tiles(256, 256), 256) * (850 + 118 * nst + 70 * nlr);
+    const long c64 = t64 <= 256 ? 540 + 46 * nst + 50 * nlr : rounds(t64, 512) * (540 + 75 * nst + 70 * nlr);
+    const long c128 = t128 <= 256 ? 620 + (nst > 28 ? 87 : 68) * nst + 70 * nlr
+                                  : rounds(t128, 512) * (620 + 108 * nst + 70 * nlr);
+    if (!pipe || std::min(c64, c128) < c256)
+      return launch_gemm_fp4_tile(bwd, c64 <= c128 ? 64 : 128, a, as, wq, ws, M, N, K, P, R, lr, bias, out, out_f32, st);
+  }
+  if (pipe) {
     const unsigned grid = (unsigned)(tm * tn);
     const GemmEpilogue none{};
     const uint16_t* b = bwd ? nullptr : bias;
@@ -1252,12 +1277,6 @@ hipError_t launch_gemm_fp4(bool bwd, const uint8_t* a, const uint8_t* as, const 
     else k_gemm_fp4_generic<true, false><<<grid, 256, 0, st>>>(a, as, wq, ws, M, N, K, P, R, lr, nullptr, out);
   }
   return hipGetLastError();
-}
-
-static bool pipe_ok(bool bwd, int M, int N, int K, int R) {
-  const int NO = bwd ? K : N, KR = bwd ? N : K;
-  return KR % 128 == 0 && K % 128 == 0 && (size_t)M * KR / 2 < (1u << 31) && (size_t)N * K / 2 < (1u << 31) &&
-         (size_t)M * (R > 0 ? R : 1) * 4 < (1u << 31) && (size_t)M * NO * 2 < (1u << 31);
 }
 
 bool gemm_fp4_fused_supported(bool bwd, int M, int N, int K, int R, int R2) {
