@@ -7,11 +7,11 @@ single-stream blocks is a triple-branch layer (frozen MXFP4 weight, frozen
 low-rank stabilizer, trainable LoRA) whose forward and backward run in the
 library's kernels through the C ABI, wrapped as torch autograd functions; the
 MLPs of the double blocks use the fused GELU / dGELU epilogues (Sec. 3.3,
-MLP fusion).  The rest of a DiT block is not part of the paper's method and
-runs as torch operations: LayerNorm with adaLN modulation, RMSNorm of q and
-k, rotary position embeddings, joint attention (fused attention kernels
-only), gated residuals.  AdamW updates the LoRA factors (fp32 masters; the
-library reads their bf16 copies).
+MLP fusion).  The rest of a DiT block is not part of the paper's method:
+LayerNorm with adaLN modulation, RMSNorm of q and k, rotary position
+embeddings and gated residuals run on fused kernels (_dit_ops), joint
+attention as a torch operation (fused attention kernels only).  AdamW updates
+the LoRA factors (fp32 masters; the library reads their bf16 copies).
 
 The same model with 16-bit LoRA linears (bf16 weights and adapters as torch
 matmuls) is the paper's BF16 LoRA baseline.
@@ -26,6 +26,7 @@ from dataclasses import dataclass
 import torch
 import torch.nn.functional as F
 
+from . import _dit_ops as ops
 from . import _lib
 
 BF = torch.bfloat16
@@ -190,27 +191,6 @@ class Bf16LoraMLP(torch.nn.Module):
 
 
 # -------------------------------------------------------------------- blocks
-def _layer_norm(x):
-    return F.layer_norm(x.float(), (x.shape[-1],), eps=1e-6)
-
-
-def _modulate(x, shift, scale):
-    return (_layer_norm(x) * (1.0 + scale.float()) + shift.float()).to(BF)
-
-
-def _rms_norm(x, w):
-    xf = x.float()
-    return (xf * torch.rsqrt(xf.pow(2).mean(-1, keepdim=True) + 1e-6) * w.float()).to(BF)
-
-
-def _rope(x, cos, sin):
-    """Rotary embedding on consecutive pairs of the head dimension:
-    x [tokens, heads, head_dim]; cos, sin [tokens, 1, head_dim / 2]."""
-    xf = x.float().unflatten(-1, (-1, 2))
-    x0, x1 = xf[..., 0], xf[..., 1]
-    return torch.stack([x0 * cos - x1 * sin, x0 * sin + x1 * cos], -1).flatten(-2).to(BF)
-
-
 def rope_tables(cfg, device):
     """FLUX's three-axis rotary table (axes of 16, 56 and 56 of the 128 head
     dimensions: a text index, then the image's row and column); text tokens
@@ -260,19 +240,15 @@ class DoubleBlock(torch.nn.Module):
         mods, qkv = {}, {}
         for s in ("img", "txt"):
             mods[s] = (F.silu(vec) @ self.mod[s]).chunk(6, -1)
-            sh1, sc1 = mods[s][0], mods[s][1]
-            q, k, v = self.qkv[s](_modulate(x[s], sh1, sc1)).view(-1, 3, cfg.heads, cfg.head_dim).unbind(1)
-            qkv[s] = (_rms_norm(q, self.qn[s]), _rms_norm(k, self.kn[s]), v)
-        cos, sin = rope
-        q = _rope(torch.cat([qkv["txt"][0], qkv["img"][0]], 0), cos, sin)
-        k = _rope(torch.cat([qkv["txt"][1], qkv["img"][1]], 0), cos, sin)
-        v = torch.cat([qkv["txt"][2], qkv["img"][2]], 0)
+            qkv[s] = self.qkv[s](ops.modulate(x[s], mods[s][0], mods[s][1]))
+        norms = [(self.qn[s], self.kn[s]) for s in ("txt", "img")]
+        q, k, v = ops.joint_qkv(qkv["txt"], qkv["img"], norms, *rope, cfg.heads, cfg.head_dim)
         o = _attention(q, k, v)
         att = {"txt": o[:cfg.txt_tokens], "img": o[cfg.txt_tokens:]}
         for s in ("img", "txt"):
             _, _, g1, sh2, sc2, g2 = mods[s]
-            x[s] = x[s] + g1 * self.out[s](att[s])
-            x[s] = x[s] + g2 * self.mlp[s](_modulate(x[s], sh2, sc2))
+            x[s] = ops.gated_residual(x[s], g1, self.out[s](att[s]))
+            x[s] = ops.gated_residual(x[s], g2, self.mlp[s](ops.modulate(x[s], sh2, sc2)))
         return x["img"], x["txt"]
 
 
@@ -292,12 +268,9 @@ class SingleBlock(torch.nn.Module):
     def forward(self, x, vec, rope):
         cfg = self.cfg
         sh, sc, g = (F.silu(vec) @ self.mod).chunk(3, -1)
-        h = self.linear1(_modulate(x, sh, sc))
-        qkv, mlp = h.split([3 * cfg.hidden, cfg.mlp], -1)
-        q, k, v = qkv.reshape(-1, 3, cfg.heads, cfg.head_dim).unbind(1)
-        cos, sin = rope
-        o = _attention(_rope(_rms_norm(q, self.qn), cos, sin), _rope(_rms_norm(k, self.kn), cos, sin), v)
-        return x + g * self.linear2(torch.cat([o, F.gelu(mlp, approximate="tanh")], -1))
+        h = self.linear1(ops.modulate(x, sh, sc))
+        c = ops.single_stream_mix(h, self.qn, self.kn, *rope, cfg.heads, cfg.head_dim, cfg.hidden, _attention)
+        return ops.gated_residual(x, g, self.linear2(c))
 
 
 class DiT(torch.nn.Module):
