@@ -1,5 +1,5 @@
-"""The DiT block's work between its linears on fused kernels (csrc/dit_ops.hip),
-as autograd functions, and the torch operations they stand for.
+"""The DiT block's work between its linears on kernels of the library
+(csrc/dit_ops.hip, csrc/attention.hip), as autograd functions, and the torch operations they stand for.
 
 Each public function here takes the fused path when its inputs are what the
 kernels hold (contiguous bf16 on one GPU, widths in range, modulation, norm
@@ -24,6 +24,8 @@ _SIGNATURES = {
     "ftdit_qkv": [_P] + [_I] * 6 + [_P] * 8 + [_P],
     "ftdit_qkv_bwd": [_P] + [_I] * 6 + [_P] * 4 + [_P, _I, _I] * 3 + [_P, _P, _P],
     "ftdit_gate": [_P, _P, _P, _P, _I, _I, _P],
+    "ftdit_attn_fwd": [_I, _I] + [_P, _I, _I] * 3 + [_P, _I, _P, _P],
+    "ftdit_attn_bwd": [_I, _I] + [_P, _I, _I] * 4 + [_P, _I] + [_P] * 6,
 }
 _ready = None
 
@@ -269,6 +271,68 @@ class _QkvGelu(torch.autograd.Function):
         return (dh,) + (None,) * 6
 
 
+# ------------------------------------------------------------------- attention
+def _rows(t):
+    """(pointer, token stride, head stride) of a [tokens, heads, 128] tensor."""
+    return t, t.stride(0), t.stride(1)
+
+
+def _attention_ok(*qkv):
+    q = qkv[0]
+    if not (_untraced() and q.is_cuda and q.dim() == 3 and q.numel() and q.shape[2] == 128 and
+            q.shape[0] * q.shape[1] < 1 << 27):
+        return False
+    for t in qkv:
+        if type(t) is not torch.Tensor or t.dtype != BF or t.device != q.device or t.shape != q.shape or \
+                t.stride(2) != 1 or t.stride(0) % 8 or t.stride(1) % 8 or t.data_ptr() % 16 or \
+                (q.shape[0] + 63) * t.stride(0) * 2 + 256 >= 1 << 31:
+            return False
+    return True
+
+
+class _Attention(torch.autograd.Function):
+    """softmax(q k^T / sqrt(128)) v over all tokens into the first columns of c [tokens, >= heads * 128]."""
+
+    @staticmethod
+    def forward(ctx, c, q, k, v):
+        L, heads, _ = q.shape
+        lse = torch.empty((heads, L), dtype=torch.float32, device=q.device)
+        _call("ftdit_attn_fwd", q.device, L, heads, *_rows(q), *_rows(k), *_rows(v), c, c.stride(0), lse)
+        ctx.mark_dirty(c)
+        ctx.save_for_backward(c, q, k, v, lse)
+        return c
+
+    @staticmethod
+    @torch.autograd.function.once_differentiable
+    def backward(ctx, dc):
+        c, q, k, v, lse = ctx.saved_tensors
+        L, heads, hd = q.shape
+        g = dc[:, :heads * hd].view(L, heads, hd) if dc.stride(1) == 1 else dc[:, :heads * hd].reshape(L, heads, hd)
+        g = _strided(g)
+        dq, dk, dv = (torch.empty((L, heads, hd), dtype=BF, device=q.device) for _ in range(3))
+        delta = torch.empty_like(lse)
+        _call("ftdit_attn_bwd", q.device, L, heads, *_rows(q), *_rows(k), *_rows(v), *_rows(g), c, c.stride(0), lse, delta,
+              dq, dk, dv)
+        return dc if ctx.needs_input_grad[0] else None, dq, dk, dv
+
+
+def torch_attention(q, k, v):
+    """Fused attention kernels only (no unfused matmul fallback)."""
+    from torch.nn.attention import SDPBackend, sdpa_kernel
+    q, k, v = (t.transpose(0, 1).unsqueeze(0) for t in (q, k, v))     # [1, heads, L, hd]
+    with sdpa_kernel([SDPBackend.FLASH_ATTENTION, SDPBackend.EFFICIENT_ATTENTION]):
+        o = F.scaled_dot_product_attention(q, k, v)
+    return o.squeeze(0).transpose(0, 1).reshape(q.shape[2], -1)
+
+
+def attention(q, k, v):
+    """Joint attention over all tokens; q, k, v [L, heads, head_dim] bf16; returns [L, heads * head_dim]."""
+    if _attention_ok(q, k, v):
+        c = torch.empty((q.shape[0], q.shape[1] * q.shape[2]), dtype=BF, device=q.device)
+        return _Attention.apply(c, q, k, v)
+    return torch_attention(q, k, v)
+
+
 class _FillLeft(torch.autograd.Function):
     """c with o in its first columns (in place: they held nothing)."""
 
@@ -284,12 +348,14 @@ class _FillLeft(torch.autograd.Function):
         return dc, dc[:, :ctx.width]
 
 
-def single_stream_mix(h, qn, kn, cos, sin, heads, hd, hidden, attention):
-    """The single-stream block between its linears: [attention(q, k, v) | GELU(mlp)] of h [T, 3 hidden + mlp]."""
+def single_stream_mix(h, qn, kn, cos, sin, heads, hd, hidden, mix=attention):
+    """The single-stream block between its linears: [mix(q, k, v) | GELU(mlp)] of h [T, 3 hidden + mlp]."""
     if _untraced() and h.is_cuda and h.dim() == 2 and h.shape[0] and 3 * hidden < h.shape[1] < 1 << 24 and \
             h.shape[1] % 8 == 0 and hidden == heads * hd < 1 << 20 and _plain(BF, h.device, h) and \
             _heads_ok(hd, h.shape[0], cos, sin, (qn, kn), h.device) and _constant(qn, kn, cos, sin):
         q, k, v, c = _QkvGelu.apply(h, qn, kn, cos, sin, heads, hidden)
-        return _FillLeft.apply(c, attention(q, k, v))
+        if mix is attention and _attention_ok(q, k, v):
+            return _Attention.apply(c, q, k, v)
+        return _FillLeft.apply(c, mix(q, k, v))
     q, k, v, m = torch_qkv_gelu(h, qn, kn, cos, sin, heads, hd, hidden)
-    return torch.cat([attention(q, k, v), m], -1)
+    return torch.cat([mix(q, k, v), m], -1)

@@ -9,8 +9,8 @@ library's kernels through the C ABI, wrapped as torch autograd functions; the
 MLPs of the double blocks use the fused GELU / dGELU epilogues (Sec. 3.3,
 MLP fusion).  The rest of a DiT block is not part of the paper's method:
 LayerNorm with adaLN modulation, RMSNorm of q and k, rotary position
-embeddings and gated residuals run on fused kernels (_dit_ops), joint
-attention as a torch operation (fused attention kernels only).  AdamW updates
+embeddings, joint attention and gated residuals run on kernels of their own
+(_dit_ops).  AdamW updates
 the LoRA factors (fp32 masters; the library reads their bf16 copies).
 
 The same model with 16-bit LoRA linears (bf16 weights and adapters as torch
@@ -210,16 +210,6 @@ def rope_tables(cfg, device):
     return torch.cos(ang), torch.sin(ang)
 
 
-def _attention(q, k, v):
-    """Joint attention over all tokens; q, k, v [L, heads, head_dim] bf16.
-    Only fused attention kernels are allowed (no unfused matmul fallback)."""
-    from torch.nn.attention import SDPBackend, sdpa_kernel
-    q, k, v = (t.transpose(0, 1).unsqueeze(0) for t in (q, k, v))     # [1, heads, L, hd]
-    with sdpa_kernel([SDPBackend.FLASH_ATTENTION, SDPBackend.EFFICIENT_ATTENTION]):
-        o = F.scaled_dot_product_attention(q, k, v)
-    return o.squeeze(0).transpose(0, 1).reshape(q.shape[2], -1)
-
-
 class DoubleBlock(torch.nn.Module):
     """Image and text streams with their own weights, joint attention."""
 
@@ -243,7 +233,7 @@ class DoubleBlock(torch.nn.Module):
             qkv[s] = self.qkv[s](ops.modulate(x[s], mods[s][0], mods[s][1]))
         norms = [(self.qn[s], self.kn[s]) for s in ("txt", "img")]
         q, k, v = ops.joint_qkv(qkv["txt"], qkv["img"], norms, *rope, cfg.heads, cfg.head_dim)
-        o = _attention(q, k, v)
+        o = ops.attention(q, k, v)
         att = {"txt": o[:cfg.txt_tokens], "img": o[cfg.txt_tokens:]}
         for s in ("img", "txt"):
             _, _, g1, sh2, sc2, g2 = mods[s]
@@ -269,7 +259,7 @@ class SingleBlock(torch.nn.Module):
         cfg = self.cfg
         sh, sc, g = (F.silu(vec) @ self.mod).chunk(3, -1)
         h = self.linear1(ops.modulate(x, sh, sc))
-        c = ops.single_stream_mix(h, self.qn, self.kn, *rope, cfg.heads, cfg.head_dim, cfg.hidden, _attention)
+        c = ops.single_stream_mix(h, self.qn, self.kn, *rope, cfg.heads, cfg.head_dim, cfg.hidden)
         return ops.gated_residual(x, g, self.linear2(c))
 
 

@@ -123,6 +123,57 @@ def test_single_stream_mix(T, heads, hd, Fm):
 
 
 @gpu
+@pytest.mark.parametrize("L,heads,gain", [(1, 2, 1.0), (64, 1, 1.0), (65, 3, 1.0), (300, 8, 4.0), (1000, 2, 1.0),
+                                          (1300, 24, 1.0)])    # the last with two key tiles per wave
+def test_attention(L, heads, gain):
+    q, k = (rnd((L, heads, 128), 1 + i, gain).requires_grad_(True) for i in range(2))
+    h = rnd((L, 4 * heads * 128), 3)
+    v = h[:, heads * 128:2 * heads * 128].view(L, heads, 128).detach().requires_grad_(True)    # strided, as in a block
+    g = rnd((L, 3 * heads * 128), 4, 1e-3)[:, :heads * 128]
+    runs = []
+    for _ in range(2):
+        q.grad = k.grad = v.grad = None
+        o = ops.attention(q, k, v)
+        assert type(o.grad_fn).__name__ == "_AttentionBackward"
+        o.backward(g)
+        runs.append([o.detach().clone(), q.grad, k.grad, v.grad])
+    assert all(torch.equal(a, b) for a, b in zip(*runs))       # fixed summation orders
+    Q, K, V = (t.detach().double().requires_grad_(True) for t in (q, k, v))
+    ref = torch.cat([torch.softmax(Q[:, i] @ K[:, i].T * 128 ** -0.5, -1) @ V[:, i] for i in range(heads)], -1)
+    ref.backward(g.double())
+    # p and ds are rounded to bf16 once before their products, and the result once; ds = p (dp - delta) cancels where
+    # the scores are sharp (gain 4), which the bf16 rounding of the result o in delta sees
+    tol = TOL2 * (1.0 if gain == 1.0 else 4.0)
+    assert relerr(runs[0][0], ref.detach()) < TOL2
+    for got, want in zip(runs[0][1:], (Q.grad, K.grad, V.grad)):
+        # (one token: dq and dk are exactly zero in the reference)
+        assert got.double().norm() < 1e-5 if L == 1 and want.norm() < 1e-9 else relerr(got, want) < tol
+
+
+@gpu
+def test_attention_where_every_score_is_far_below_zero():
+    """Scores near -300: the stage's rows past the last key (whose score is 0) must not reach dq."""
+    a = rnd((1, 2, 128), 1).float() * 5.2
+    q, k = ((s * a + rnd((70, 2, 128), 2 + i).float()).to(BF).requires_grad_(True) for i, s in enumerate((1.0, -1.0)))
+    v, g = rnd((70, 2, 128), 4).requires_grad_(True), rnd((70, 256), 5)
+    o = ops.attention(q, k, v)
+    o.backward(g)
+    Q, K, V = (t.detach().double().requires_grad_(True) for t in (q, k, v))
+    s = Q[:, 0] @ K[:, 0].T * 128 ** -0.5
+    assert s.max() < -150
+    ref = torch.cat([torch.softmax(Q[:, i] @ K[:, i].T * 128 ** -0.5, -1) @ V[:, i] for i in range(2)], -1)
+    ref.backward(g.double())
+    for got, want in ((o.detach(), ref.detach()), (q.grad, Q.grad), (k.grad, K.grad), (v.grad, V.grad)):
+        assert bool(torch.isfinite(got).all()) and relerr(got, want) < 8 * TOL2
+
+
+@gpu
+def test_attention_of_other_shapes_is_the_library_s():
+    q, k, v = (rnd((40, 2, 64), 1 + i) for i in range(3))
+    assert torch.equal(ops.attention(q, k, v), ops.torch_attention(q, k, v))
+
+
+@gpu
 def test_calls_that_stay_torch_operations():
     """Gradients of the modulation, other types and layouts, widths past the
     kernel's, functional transforms and a differentiated backward."""
