@@ -196,8 +196,8 @@ ft_status ft_linear_bwd_input(const uint8_t *gq, const uint8_t *gs, int64_t M, i
 
 /*
  * MLP pair, forward of FC1 fused with FC2's input preparation (Sec. 3.3, MLP
- * fusion: the GELU and FC2's quantization and down-projection consume FC1's
- * output tile while it is on chip).  The GEMM is ft_linear_fwd's; then
+ * fusion: the GELU and FC2's quantization and down-projection share one pass
+ * over FC1's output).  The GEMM is ft_linear_fwd's; then
  *   z[m,n]   = bf16(y[m,n])                         saved for the backward
  *   h[m,n]   = bf16(GELU_tanh(z[m,n]))              FC2's input
  *   hq, hs   = 1x32 MXFP4 codes/scales of h (as ft_quantize_blockwise)
@@ -208,8 +208,8 @@ ft_status ft_linear_bwd_input(const uint8_t *gq, const uint8_t *gs, int64_t M, i
  *   [M, N/2]; hs uint8 [M, N/32].  D2: bf16 [N, R2] = FC2's [L1 | A];
  *   R2 in {0, 16, 32, 48, 64} (0: no projection, D2 and P2 NULL);  P2 fp32 [M, R2].
  *   workspace: ft_linear_fwd_gelu_workspace_size(M, N, R2) bytes, 16-byte
- *   aligned (NULL when 0): per-column-tile partials of P2, summed in a fixed
- *   order by a second kernel.
+ *   aligned (NULL when 0): partials of P2 over column runs, summed in a fixed
+ *   order by a further kernel.
  * Needs K % 128 == 0 (FT_ERR_UNSUPPORTED otherwise).
  */
 ft_status ft_linear_fwd_gelu(const uint8_t *xq, const uint8_t *xs, int64_t M, int64_t K,
@@ -222,7 +222,8 @@ size_t ft_linear_fwd_gelu_workspace_size(int64_t M, int64_t N, int32_t R2);
 
 /*
  * MLP pair, backward-input of FC2 fused with FC1's gradient preparation: the
- * GEMM is ft_linear_bwd_input's (its fp32 result dH is not rounded), then
+ * GEMM is ft_linear_bwd_input's (its fp32 result dH is not rounded; GELU' is
+ * applied in its epilogue), then
  *   dz[m,k]  = bf16(dH[m,k] * GELU_tanh'(z[m,k]))   FC1's incoming gradient
  *   dzq, dzs = 1x32 MXFP4 codes/scales of dz
  *   Qp1[m,j] = sum_k dz[m,k] U1[j,k]                 FC1's Qp (fp32)

@@ -159,7 +159,7 @@ ft_status ft_linear_fwd(const uint8_t* xq, const uint8_t* xs, int64_t M, int64_t
     return fail(FT_ERR_ALIGN, "xq, xs, wq, ws, y, bias must be 16-byte aligned");
   FT_TRY(check_rank(R, P, U, "P", "U"));
   return hip_status(ft::launch_gemm_fp4(false, xq, xs, wq, ws, (int)M, (int)N, (int)K, P, R, (const uint16_t*)U,
-                                        (const uint16_t*)bias, y, y_dtype == FT_F32, stream),
+                                        (const uint16_t*)bias, y, y_dtype == FT_F32, nullptr, stream),
                     "linear fwd");
 }
 
@@ -178,7 +178,7 @@ ft_status ft_linear_bwd_input(const uint8_t* gq, const uint8_t* gs, int64_t M, i
     return fail(FT_ERR_ALIGN, "gq, gs, wq, ws, dx must be 16-byte aligned");
   FT_TRY(check_rank(R, Qp, D, "Qp", "D"));
   return hip_status(ft::launch_gemm_fp4(true, gq, gs, wq, ws, (int)M, (int)N, (int)K, Qp, R, (const uint16_t*)D,
-                                        nullptr, dx, dx_dtype == FT_F32, stream),
+                                        nullptr, dx, dx_dtype == FT_F32, nullptr, stream),
                     "linear bwd input");
 }
 
@@ -210,11 +210,12 @@ ft_status ft_linear_fwd_gelu(const uint8_t* xq, const uint8_t* xs, int64_t M, in
   if (!ft::gemm_fp4_fused_supported(false, (int)M, (int)N, (int)K, R, R2))
     return fail(FT_ERR_UNSUPPORTED, "fused GELU epilogue needs K %% 128 == 0 and operands below 2 GiB");
   FT_TRY(check_workspace(workspace, workspace_bytes, mlp_workspace(M, N, R2)));
-  const bool parts = mlp_workspace(M, N, R2) > 0;
-  ft::GemmEpilogue ep{(uint16_t*)z, nullptr, (uint16_t*)h, hq, hs, (const uint16_t*)D2, R2, parts ? (float*)workspace : P2};
-  return hip_status(ft::launch_gemm_fp4_fused(false, xq, xs, wq, ws, (int)M, (int)N, (int)K, P, R, (const uint16_t*)U,
-                                              (const uint16_t*)bias, ep, P2, stream),
-                    "linear fwd gelu");
+  FT_TRY(hip_status(ft::launch_gemm_fp4(false, xq, xs, wq, ws, (int)M, (int)N, (int)K, P, R, (const uint16_t*)U,
+                                        (const uint16_t*)bias, z, false, nullptr, stream),
+                    "linear fwd gelu"));
+  return hip_status(ft::launch_quant_gelu((const uint16_t*)z, (int)M, (int)N, (uint16_t*)h, hq, hs, (const uint16_t*)D2,
+                                          R2, P2, (float*)workspace, ft::gemm_fp4_col_tiles((int)N), stream),
+                    "linear fwd gelu (quantize)");
 }
 
 size_t ft_linear_bwd_input_dgelu_workspace_size(int64_t M, int64_t K, int32_t R1) { return mlp_workspace(M, K, R1); }
@@ -240,12 +241,12 @@ ft_status ft_linear_bwd_input_dgelu(const uint8_t* gq, const uint8_t* gs, int64_
   if (!ft::gemm_fp4_fused_supported(true, (int)M, (int)N, (int)K, R, R1))
     return fail(FT_ERR_UNSUPPORTED, "fused dGELU epilogue needs N and K multiples of 128 and operands below 2 GiB");
   FT_TRY(check_workspace(workspace, workspace_bytes, mlp_workspace(M, K, R1)));
-  const bool parts = mlp_workspace(M, K, R1) > 0;
-  ft::GemmEpilogue ep{nullptr, (const uint16_t*)z, (uint16_t*)dz, dzq, dzs, (const uint16_t*)U1, R1,
-                      parts ? (float*)workspace : Qp1};
-  return hip_status(ft::launch_gemm_fp4_fused(true, gq, gs, wq, ws, (int)M, (int)N, (int)K, Qp, R, (const uint16_t*)D,
-                                              nullptr, ep, Qp1, stream),
-                    "linear bwd input dgelu");
+  FT_TRY(hip_status(ft::launch_gemm_fp4(true, gq, gs, wq, ws, (int)M, (int)N, (int)K, Qp, R, (const uint16_t*)D,
+                                        nullptr, dz, false, (const uint16_t*)z, stream),
+                    "linear bwd input dgelu"));
+  return hip_status(ft::launch_quant_rows((const uint16_t*)dz, (int)M, (int)K, dzq, dzs, (const uint16_t*)U1, R1,
+                                          FT_PROJ_R_BY_COLS, Qp1, (float*)workspace, stream),
+                    "linear bwd input dgelu (quantize)");
 }
 
 size_t ft_lora_grads_workspace_size(int64_t M, int64_t K, int64_t N, int64_t ld, int32_t r) {

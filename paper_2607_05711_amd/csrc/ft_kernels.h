@@ -23,6 +23,17 @@ size_t quant_rows_workspace(int rows, int cols, int R, int layout);
 hipError_t launch_quant_rows(const uint16_t* src, int rows, int cols, uint8_t* codes, uint8_t* scales,
                              const uint16_t* proj, int R, int layout, float* proj_out, float* ws, hipStream_t st,
                              const QuantMode& mode = QuantMode{});
+// h = bf16(GELU(z)) stored and quantized, with the projection h . proj [cols, R]
+// (R = 0: none; R <= 128); ws holds max_groups partials.
+hipError_t launch_quant_gelu(const uint16_t* z, int rows, int cols, uint16_t* h, uint8_t* codes, uint8_t* scales,
+                             const uint16_t* proj, int R, float* proj_out, float* ws, int max_groups, hipStream_t st);
+// Streaming form of the row quantization with a projection (nearest-even
+// rounding): at most max_groups partials in ws.  gelu_out: src is z, h =
+// bf16(GELU(z)) is stored there and quantized (layout 0).
+bool quant_proj_supported(int rows, int cols, int R);
+hipError_t launch_quant_proj(const uint16_t* src, int rows, int cols, uint8_t* codes, uint8_t* scales,
+                             const uint16_t* proj, int R, int layout, bool no_clip, float* proj_out, float* ws,
+                             int max_groups, uint16_t* gelu_out, hipStream_t st);
 hipError_t launch_quant_tiles(const uint16_t* src, int rows, int cols, uint8_t* codes, uint8_t* scales,
                               hipStream_t st, const QuantMode& mode = QuantMode{});
 
@@ -32,36 +43,21 @@ hipError_t launch_reduce_parts(const float* ws, int nparts, size_t n0, float* ou
 
 // FP4 GEMM.  bwd = false: out[M, N] = A[M, K] . W[N, K]^T  (+ P . U + bias)
 //            bwd = true : out[M, K] = A[M, N] . W[N, K]    (+ P . D^T)
+// z (bwd, bf16 out; NULL for none): out = bf16(that result * GELU'(z)), z bf16
+// [M, K]; needs gemm_fp4_fused_supported.
 hipError_t launch_gemm_fp4(bool bwd, const uint8_t* a, const uint8_t* as, const uint8_t* wq, const uint8_t* ws,
                            int M, int N, int K, const float* P, int R, const uint16_t* lr,
-                           const uint16_t* bias, void* out, bool out_f32, hipStream_t st);
-
+                           const uint16_t* bias, void* out, bool out_f32, const uint16_t* z, hipStream_t st);
 // The same product on tm x 128 output tiles (tm = 64 or 128), any K and N that are
 // multiples of 32; whether its 32-bit offsets and LDS hold this shape.
 bool gemm_fp4_tile_supported(bool bwd, int M, int N, int K, int R, bool out_f32);
 hipError_t launch_gemm_fp4_tile(bool bwd, int tm, const uint8_t* a, const uint8_t* as, const uint8_t* wq,
                                 const uint8_t* ws, int M, int N, int K, const float* P, int R, const uint16_t* lr,
-                                const uint16_t* bias, void* out, bool out_f32, hipStream_t st);
-
-// Epilogues of the MLP pair (the output NO columns feed the next linear).
-enum { EPI_PLAIN = 0, EPI_GELU = 1, EPI_DGELU = 2 };
-struct GemmEpilogue {
-  uint16_t* z_out;        // EPI_GELU: z = bf16(acc) [M, NO]
-  const uint16_t* z_in;   // EPI_DGELU: z saved by the forward [M, NO]
-  uint16_t* y;            // EPI_GELU: h = bf16(GELU(z));  EPI_DGELU: dz = bf16(acc GELU'(z))  [M, NO]
-  uint8_t* q;             // E2M1 codes of y [M, NO/2]
-  uint8_t* s;             // E8M0 scales of y [M, NO/32]
-  const uint16_t* proj;   // EPI_GELU: D2 [NO, R2];  EPI_DGELU: U1 [R2, NO];  unused when R2 == 0
-  int R2;                 // 0, 16, 32, 48 or 64
-  float* parts;           // fp32 partials [tiles over NO][M][R2], or the projection when one tile spans NO
-};
-// Whether the fused epilogues support this shape (the pipelined kernel runs it).
+                                const uint16_t* bias, void* out, bool out_f32, const uint16_t* z, hipStream_t st);
+// Whether the MLP pair's calls take this shape, and the number of projection
+// partials that their workspace holds.
 bool gemm_fp4_fused_supported(bool bwd, int M, int N, int K, int R, int R2);
-// Number of output column tiles (partials of the fused projection).
 int gemm_fp4_col_tiles(int NO);
-hipError_t launch_gemm_fp4_fused(bool bwd, const uint8_t* a, const uint8_t* as, const uint8_t* wq, const uint8_t* ws,
-                                 int M, int N, int K, const float* P, int R, const uint16_t* lr, const uint16_t* bias,
-                                 const GemmEpilogue& ep, float* proj_out, hipStream_t st);
 
 // Adapter gradients; token chunks leave partials in ws (lora_grads_workspace bytes).
 size_t lora_grads_workspace(int M, int K, int N, int ld, int r);

@@ -69,7 +69,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_fp4_tile(const uint8_t* __restr
                                                           int M, int N, int K, const float* __restrict__ P, int R,
                                                           const uint16_t* __restrict__ LR,
                                                           const uint16_t* __restrict__ bias, void* __restrict__ out,
-                                                          int out_f32, int tiles_m, int tiles_n) {
+                                                          int out_f32, int tiles_m, int tiles_n,
+                                                          const uint16_t* __restrict__ z) {
   using G = TileGeom<TM>;
   extern __shared__ __attribute__((aligned(16))) uint8_t tlds[];
   constexpr int MT = TM / 64, NT = 2;                // 32x32 MFMA tiles per wave
@@ -438,21 +439,34 @@ __global__ __launch_bounds__(256, 2) void k_gemm_fp4_tile(const uint8_t* __restr
 
   // ---------------- epilogue: 32 rows at a time through the wave's own LDS
   __syncthreads();   // all waves are done with the ring
-  auto store = [&](auto f32c) {
-    constexpr bool OUT_F32 = decltype(f32c)::value != 0;
-    constexpr int ES = OUT_F32 ? 4 : 2;
+  // OUT: 0 bf16, 1 fp32, 2 bf16(result * GELU'(z)) (staged as fp32).
+  auto store = [&](auto outc) {
+    constexpr int OUT = decltype(outc)::value;
+    constexpr int ES = OUT == 0 ? 2 : 4;               // staged element
     constexpr int SROW = 64 * ES + 16;
     constexpr int CH = 64 * ES / 16, RPI = 64 / CH;    // 16-byte chunks per row, rows per load
     uint8_t* stg = tlds + wave * (32 * SROW);
-    const __amdgpu_buffer_rsrc_t ro = make_rsrc(out, (uint32_t)M * NO * ES);
+    const __amdgpu_buffer_rsrc_t ro = make_rsrc(out, (uint32_t)M * NO * (OUT == 1 ? 4 : 2));
+    const __amdgpu_buffer_rsrc_t rz = make_rsrc(z, OUT == 2 ? (uint32_t)M * NO * 2 : 0u);
 #pragma unroll
     for (int i = 0; i < MT; i++) {
+      // element offset of this lane's chunk `it` in the output, or none
+      auto at = [&](int it) {
+        const int gr = m0 + wm * (TM / 2) + 32 * i + it * RPI + lane / CH, gc = n0 + wn * 64 + (lane % CH) * (16 / ES);
+        return gr < M && gc < NO ? (uint32_t)gr * NO + gc : kOobOffset;
+      };
+      v2i zv[32 / RPI];
+      if constexpr (OUT == 2) {
+#pragma unroll
+        for (int it = 0; it < 32 / RPI; it++)
+          zv[it] = __builtin_bit_cast(v2i, __builtin_amdgcn_raw_buffer_load_b64(rz, at(it) == kOobOffset ? kOobOffset : at(it) * 2, 0, 0));
+      }
 #pragma unroll
       for (int j = 0; j < NT; j++)
 #pragma unroll
         for (int q = 0; q < 4; q++) {
           const int col = 32 * j + 8 * q + 4 * h;
-          if constexpr (OUT_F32) {
+          if constexpr (OUT != 0) {
             *(v4f*)(stg + r32 * SROW + col * 4) =
                 v4f{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
           } else {
@@ -465,14 +479,26 @@ __global__ __launch_bounds__(256, 2) void k_gemm_fp4_tile(const uint8_t* __restr
       __builtin_amdgcn_s_waitcnt(0xc07f);  // the wave reads back only its own rows
 #pragma unroll
       for (int it = 0; it < 32 / RPI; it++) {
-        const int rr = it * RPI + lane / CH, c = lane % CH;
-        const v4i seg = *(const v4i*)(stg + rr * SROW + c * 16);
-        const int gr = m0 + wm * (TM / 2) + 32 * i + rr, gc = n0 + wn * 64 + c * (16 / ES);
-        __builtin_amdgcn_raw_buffer_store_b128(seg, ro, gr < M && gc < NO ? ((uint32_t)gr * NO + gc) * ES : kOobOffset, 0, 0);
+        const v4i seg = *(const v4i*)(stg + (it * RPI + lane / CH) * SROW + (lane % CH) * 16);
+        const uint32_t off = at(it);
+        if constexpr (OUT == 2) {
+          const v4f d = __builtin_bit_cast(v4f, seg);
+          v2i w;
+#pragma unroll
+          for (int e = 0; e < 2; e++) {
+            const v2f dv = {d[2 * e] * gelu_tanh_grad(bf16_to_f32((uint32_t)zv[it][e] & 0xFFFFu)),
+                            d[2 * e + 1] * gelu_tanh_grad(bf16_to_f32((uint32_t)zv[it][e] >> 16))};
+            w[e] = (int)__builtin_bit_cast(uint32_t, __builtin_convertvector(dv, v2bf));
+          }
+          __builtin_amdgcn_raw_buffer_store_b64(w, ro, off == kOobOffset ? kOobOffset : off * 2, 0, 0);
+        } else {
+          __builtin_amdgcn_raw_buffer_store_b128(seg, ro, off == kOobOffset ? kOobOffset : off * ES, 0, 0);
+        }
       }
     }
   };
-  if (out_f32) store(IC<1>{});
+  if (z) store(IC<2>{});
+  else if (out_f32) store(IC<1>{});
   else store(IC<0>{});
 }
 
@@ -487,7 +513,7 @@ bool gemm_fp4_tile_supported(bool bwd, int M, int N, int K, int R, bool out_f32)
 
 hipError_t launch_gemm_fp4_tile(bool bwd, int tm, const uint8_t* a, const uint8_t* as, const uint8_t* wq,
                                 const uint8_t* ws, int M, int N, int K, const float* P, int R, const uint16_t* lr,
-                                const uint16_t* bias, void* out, bool out_f32, hipStream_t st) {
+                                const uint16_t* bias, void* out, bool out_f32, const uint16_t* z, hipStream_t st) {
   const int NO = bwd ? K : N, KR = bwd ? N : K;
   const int nkb = KR >> 5, nst = (KR + TK - 1) / TK;
   if (tm == 128 && slab_bytes(128, nkb, nst) + 2 * TileGeom<128>::SLOT > kCuLds) tm = 64;
@@ -500,7 +526,7 @@ hipError_t launch_gemm_fp4_tile(bool bwd, int tm, const uint8_t* a, const uint8_
   const unsigned grid = (unsigned)((tiles + 7) / 8 * 8);
 #define FT_TILE(BW, TM_, NS_) \
   k_gemm_fp4_tile<BW, TM_, NS_><<<grid, 256, (size_t)NS_ * slot + rest, st>>>(a, as, wq, ws, M, N, K, P, R, lr, bias, out, \
-                                                                          out_f32 ? 1 : 0, tiles_m, tiles_n)
+                                                                          out_f32 ? 1 : 0, tiles_m, tiles_n, z)
   if (tm == 64) {
     if (ns >= 5) { if (!bwd) FT_TILE(false, 64, 5); else FT_TILE(true, 64, 5); }
     else if (ns >= 3) { if (!bwd) FT_TILE(false, 64, 3); else FT_TILE(true, 64, 3); }

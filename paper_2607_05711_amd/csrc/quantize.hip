@@ -6,7 +6,8 @@
 // stabilizer and adapter branches share the input, so one pass reads it once).
 // Workgroups cover one column chunk, or (MC) a few consecutive ones with
 // the projection slice re-staged between them; their partial projections
-// are summed by k_reduce_parts.
+// are summed by k_reduce_parts.  With a projection and nearest-even rounding
+// the streaming kernel of quant_proj.hip takes its place.
 // k_quant_rows_fr: the same for a [cols, R] projection with whole rows per
 // workgroup, which adds its partial projections itself.
 // k_quant_tiles: 32x32 tiles of the frozen weight (Sec. 3.2), offline.
@@ -105,13 +106,16 @@ __device__ __forceinline__ void quant_step(const v4i (&x)[4], int rw0, int rows,
   }
 }
 
-template <int RT, int MODE, int WAVES, int CW, int QM, bool MC>
+// GELU: src is z; h = bf16(GELU(z)) takes its place as it is read, and is
+// stored to h_out.
+template <int RT, int MODE, int WAVES, int CW, int QM, bool MC, bool GELU = false>
 __global__ __launch_bounds__(64 * WAVES) void k_quant_rows(const uint16_t* __restrict__ src, int rows,
                                                                      int cols, uint8_t* __restrict__ codes,
                                                                      uint8_t* __restrict__ scales,
                                                                      const uint16_t* __restrict__ proj, int R,
                                                                      float* __restrict__ proj_out, float* __restrict__ parts,
-                                                                     SrKey key, int cpw) {
+                                                                     SrKey key, int cpw,
+                                                                     uint16_t* __restrict__ h_out = nullptr) {
   using L = QuantLds<RT, MODE, WAVES, CW>;
   __shared__ __attribute__((aligned(16))) uint16_t lds[L::HALFWORDS];
   constexpr int NST = CW / 64;     // 64-column steps per chunk
@@ -197,6 +201,19 @@ __global__ __launch_bounds__(64 * WAVES) void k_quant_rows(const uint16_t* __res
       if (st + PF < NST) issue(st + PF);
       const int blk = 2 * st + (lane >> 2 & 1);           // this lane's block within the chunk
       const bool col_ok = blk < nblk;
+      if constexpr (GELU) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            const uint32_t zz = (uint32_t)xv[st][q][e];
+            const v2f hv = {gelu_tanh(bf16_to_f32(zz & 0xFFFFu)), gelu_tanh(bf16_to_f32(zz >> 16))};
+            xv[st][q][e] = (int)__builtin_bit_cast(uint32_t, __builtin_convertvector(hv, v2bf));
+          }
+          const int row = rw0 + 8 * q + lr;
+          if (col_ok && row < rows) *(v4i*)(h_out + (size_t)row * cols + c0 + 64 * st + lc) = xv[st][q];
+        }
+      }
       // interior (every row of the wave and both blocks of the step in range):
       // no masking; the edge path zeroes what lies outside
       const uint64_t idx0 = (uint64_t)(rw0 + lr) * cols + c0 + 64 * st + lc;
@@ -570,11 +587,17 @@ static bool quant_full_rows(int rows, int cols, int R, int layout) {
   return layout == 0 && R > 0 && R <= 64 && cols <= 32 * QF_MAX_BLOCKS && wg >= 64 && wg <= 256;
 }
 
-size_t quant_rows_workspace(int rows, int cols, int R, int layout) {
-  if (R == 0 || quant_full_rows(rows, cols, R, layout)) return 0;
+// Workgroups along a row of the chunked kernel: the partials that the
+// workspace holds.
+static int quant_groups(int rows, int cols, int R, int layout) {
   const int cw = quant_chunk_cols(rows, cols, R, layout);
   const int cpw = quant_chunks_per_wg(rows, cols, cw, layout);
-  const int groups = ((cols + cw - 1) / cw + cpw - 1) / cpw;
+  return ((cols + cw - 1) / cw + cpw - 1) / cpw;
+}
+
+size_t quant_rows_workspace(int rows, int cols, int R, int layout) {
+  if (R == 0 || quant_full_rows(rows, cols, R, layout)) return 0;
+  const int groups = quant_groups(rows, cols, R, layout);
   return groups > 1 ? (size_t)groups * rows * R * sizeof(float) : 0;
 }
 
@@ -597,6 +620,16 @@ static hipError_t launch_rows_t(const uint16_t* src, int rows, int cols, uint8_t
   return launch_reduce_parts(parts, (int)grid.y, (size_t)rows * R, proj_out, 0, nullptr, false, st);
 }
 
+hipError_t launch_quant_gelu(const uint16_t* z, int rows, int cols, uint16_t* h, uint8_t* codes, uint8_t* scales,
+                             const uint16_t* proj, int R, float* proj_out, float* ws, int max_groups, hipStream_t st) {
+  if (R > 0)
+    return launch_quant_proj(z, rows, cols, codes, scales, proj, R, 0, false, proj_out, ws, max_groups, h, st);
+  dim3 grid((rows + 127) / 128, (cols + 383) / 384);
+  k_quant_rows<1, 0, 4, 384, 0, false, true><<<grid, 256, 0, st>>>(z, rows, cols, codes, scales, nullptr, 0, nullptr,
+                                                                  nullptr, SrKey{}, 1, h);
+  return hipGetLastError();
+}
+
 template <int QM>
 static hipError_t launch_quant_rows_qm(const uint16_t* src, int rows, int cols, uint8_t* codes, uint8_t* scales,
                                        const uint16_t* proj, int R, int layout, float* proj_out, float* ws,
@@ -614,6 +647,15 @@ static hipError_t launch_quant_rows_qm(const uint16_t* src, int rows, int cols, 
     else { if (rt == 1) FT_FR(1, 4); else FT_FR(2, 4); }
 #undef FT_FR
     return hipGetLastError();
+  }
+  // Nearest-even rounding with a projection streams (any size its 32-bit
+  // offsets reach, up to 8 million columns), with at most the partials that
+  // the workspace was sized for; stochastic rounding, bound by its arithmetic,
+  // keeps the eight waves per CU of the chunks.
+  if constexpr ((QM & QM_SR) == 0) {
+    if (quant_proj_supported(rows, cols, R))
+      return launch_quant_proj(src, rows, cols, codes, scales, proj, R, layout, (QM & QM_NOCLIP) != 0, proj_out, ws,
+                               quant_groups(rows, cols, R, layout), nullptr, st);
   }
 #define FT_ROWS(RT_, MODE_, CW_) \
   launch_rows_t<RT_, MODE_, 8, CW_, QM>(src, rows, cols, codes, scales, proj, R, proj_out, ws, key, st)

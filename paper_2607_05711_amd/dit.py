@@ -6,8 +6,8 @@ builds that step around the library: every linear of the double- and
 single-stream blocks is a triple-branch layer (frozen MXFP4 weight, frozen
 low-rank stabilizer, trainable LoRA) whose forward and backward run in the
 library's kernels through the C ABI, wrapped as torch autograd functions; the
-MLPs of the double blocks use the fused GELU / dGELU epilogues (Sec. 3.3,
-MLP fusion).  The rest of a DiT block is not part of the paper's method:
+MLPs of the double blocks use the fused GELU / dGELU calls (Sec. 3.3, MLP
+fusion).  The rest of a DiT block is not part of the paper's method:
 LayerNorm with adaLN modulation, RMSNorm of q and k, rotary position
 embeddings, joint attention and gated residuals run on kernels of their own
 (_dit_ops).  AdamW updates
@@ -78,7 +78,7 @@ class _TripleBranchFn(torch.autograd.Function):
 
 
 class _MlpPairFn(torch.autograd.Function):
-    """FC1 -> GELU(tanh) -> FC2 with the fused epilogues (MLP fusion)."""
+    """FC1 -> GELU(tanh) -> FC2 with the fused calls (MLP fusion)."""
 
     @staticmethod
     def forward(ctx, x, A1, B1, A2, B2, fc1, fc2):
@@ -139,7 +139,7 @@ class FourTuneLinear(torch.nn.Module):
 
 class FourTuneMLP(torch.nn.Module):
     """MLP pair D -> F -> D (GELU tanh) of two triple-branch linears, forward
-    and backward through the fused epilogues."""
+    and backward through the fused calls."""
 
     def __init__(self, Dm, Fm, r, rs, gen, device):
         super().__init__()
