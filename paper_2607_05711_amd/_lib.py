@@ -116,14 +116,24 @@ def _check(status):
 def _ptr(t, offset_elems=0):
     if t is None:
         return None
-    return ctypes.c_void_p(t.data_ptr() + offset_elems * t.element_size())
+    return t.data_ptr() + offset_elems * t.element_size() if offset_elems else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    """The current HIP stream of this device, as an address."""
+    if _raw_stream is not None and device.index is not None:
+        return _raw_stream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
 
 
 def _need(t, name, dtype, device=None, ndim=None):
+    # one pass for the usual case (these checks are most of a small call's host time); what fails it is named below
+    if isinstance(t, torch.Tensor) and t.dtype is dtype and t.is_cuda and t.is_contiguous() and \
+            (device is None or t.device == device) and (ndim is None or t.dim() == ndim):
+        return t
     if not isinstance(t, torch.Tensor):
         raise TypeError("%s must be a torch.Tensor" % name)
     if t.dtype != dtype:
