@@ -23,6 +23,7 @@ _SIGNATURES = {
     "ftdit_modulate_bwd": [_P, _P, _P, _P, _I, _I, _P],
     "ftdit_qkv": [_P] + [_I] * 6 + [_P] * 8 + [_P],
     "ftdit_qkv_bwd": [_P] + [_I] * 6 + [_P] * 4 + [_P, _I, _I] * 3 + [_P, _P, _P],
+    "ftdit_mod": [_P, _P, _P, _P, _I, _I, _P],
     "ftdit_gate": [_P, _P, _P, _P, _I, _I, _P],
     "ftdit_attn_fwd": [_I, _I] + [_P, _I, _I] * 3 + [_P, _I, _P, _P],
     "ftdit_attn_bwd": [_I, _I] + [_P, _I, _I] * 4 + [_P, _I] + [_P] * 6,
@@ -145,6 +146,26 @@ def modulate(x, shift, scale):
             _plain(BF, x.device, x, shift, scale) and _row(shift, x) and _row(scale, x) and _constant(shift, scale):
         return _Modulate.apply(x, shift, scale)
     return torch_modulate(x, shift, scale)
+
+
+# ----------------------------------------------------------- modulation vector
+def _mod_parts(K, N):
+    f = _lib.load().ftdit_mod_parts
+    f.argtypes, f.restype = [_I, _I], _I
+    return f(K, N)
+
+
+def modulation(vec, w):
+    """silu(vec) @ w: the block's shift, scale and gate vectors."""
+    if vec.is_cuda and _untraced() and vec.dim() > 0 and w.dim() == 2 and 0 < vec.numel() == vec.shape[-1] == w.shape[0] < 1 << 20 and \
+            0 < w.shape[1] < 1 << 24 and w.shape[1] % 8 == 0 and _plain(BF, vec.device, vec, w) and _constant(vec, w) and \
+            not torch.is_autocast_enabled("cuda"):
+        out = torch.empty(vec.shape[:-1] + w.shape[1:], dtype=BF, device=vec.device)
+        K, N = w.shape
+        parts = torch.empty((_mod_parts(K, N), N), dtype=torch.float32, device=vec.device)
+        _call("ftdit_mod", vec.device, vec, w, out, parts, K, N)
+        return out
+    return F.silu(vec) @ w
 
 
 # ------------------------------------------------------------- gated residual

@@ -229,7 +229,7 @@ class DoubleBlock(torch.nn.Module):
         x = {"img": img, "txt": txt}
         mods, qkv = {}, {}
         for s in ("img", "txt"):
-            mods[s] = (F.silu(vec) @ self.mod[s]).chunk(6, -1)
+            mods[s] = ops.modulation(vec, self.mod[s]).chunk(6, -1)
             qkv[s] = self.qkv[s](ops.modulate(x[s], mods[s][0], mods[s][1]))
         norms = [(self.qn[s], self.kn[s]) for s in ("txt", "img")]
         q, k, v = ops.joint_qkv(qkv["txt"], qkv["img"], norms, *rope, cfg.heads, cfg.head_dim)
@@ -257,7 +257,7 @@ class SingleBlock(torch.nn.Module):
 
     def forward(self, x, vec, rope):
         cfg = self.cfg
-        sh, sc, g = (F.silu(vec) @ self.mod).chunk(3, -1)
+        sh, sc, g = ops.modulation(vec, self.mod).chunk(3, -1)
         h = self.linear1(ops.modulate(x, sh, sc))
         c = ops.single_stream_mix(h, self.qn, self.kn, *rope, cfg.heads, cfg.head_dim, cfg.hidden)
         return ops.gated_residual(x, g, self.linear2(c))

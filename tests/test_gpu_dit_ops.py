@@ -73,6 +73,19 @@ def test_gated_residual(rows, H):
 
 
 @gpu
+@pytest.mark.parametrize("K,N", [(1, 8), (7, 128), (128, 136), (129, 8), (1000, 3072), (3072, 9216), (2056, 18440), (5000, 65544)])
+def test_modulation(K, N):
+    """Edges of the 128 columns and rows of a step, one and several steps a part."""
+    v, w = rnd((1, K), 1, 2.0), rnd((K, N), 2)
+    y = ops.modulation(v, w)
+    assert y.shape == (1, N) and torch.equal(y[0], ops.modulation(v[0], w))
+    s = torch.nn.functional.silu(v.double()).to(BF).double()
+    assert relerr(y, s @ w.double()) < TOL
+    for stays in (rnd((2, K), 1), rnd((1, 2 * K), 1)[:, ::2], v.clone().requires_grad_(True)):
+        assert relerr(ops.modulation(stays, w).detach(), torch.nn.functional.silu(stays.detach()) @ w) < TOL2
+
+
+@gpu
 @pytest.mark.parametrize("T1,T2,heads,hd", [(1, 1, 1, 8), (7, 30, 3, 16), (5, 12, 2, 512), (64, 200, 24, 128)])
 def test_joint_qkv(T1, T2, heads, hd):
     H = heads * hd
