@@ -967,10 +967,11 @@ __global__ __launch_bounds__(256, 1) void k_gemm_fp4_pipe(const uint8_t* __restr
     // stores, so that waiting for them waits only for the stores of pass i - 2
     // (loads and stores retire in order); all passes' loads at once made every
     // CU load its whole z tile in one burst.
-    // Bound by the vector unit: an exponential, a reciprocal and some ten
-    // operations per element on one wave per SIMD, with the matrix cores idle
-    // (4608 x 3072 -> 12288: 169 us against 102 us for the plain product).  For
-    // that reason dz is quantized and projected by the quantize kernel, not
+    // Bound by its traffic: all CUs read z and write dz in the same phase, 226
+    // MB beside the product's operands (4608 x 3072 -> 12288: 169 us against
+    // 102 us for the plain product; GELU' from an LDS table of bf16 z, some
+    // seven operations for the eleven here, two of them quarter-rate, gave 3
+    // us).  dz is quantized and projected by the quantize kernel, not
     // here: doing both here took 199 us and left 48 partials to reduce (10 us);
     // the pass over dz takes 36 us with its reduction.
     constexpr int SROW = 128 * 4 + 16;                 // staged row stride (bytes)
