@@ -358,4 +358,10 @@ ft_status ft_linear_bwd_input_nvfp4(const uint8_t* gq, const uint8_t* gs, const 
   return nvfp4_gemm(true, gq, gs, gt, M, N, wq, ws, wt, K, dx, stream);
 }
 
+// Which kernel a product runs on (see gemm_fp4_kernel): for the tests of the
+// dispatch, not part of the public header.
+int ftx_gemm_kernel(int bwd, int64_t M, int64_t N, int64_t K, int32_t R, int out_f32) {
+  return ft::gemm_fp4_kernel(bwd != 0, (int)M, (int)N, (int)K, R, out_f32 != 0);
+}
+
 }  // extern "C"

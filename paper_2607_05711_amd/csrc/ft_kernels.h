@@ -51,9 +51,15 @@ hipError_t launch_gemm_fp4(bool bwd, const uint8_t* a, const uint8_t* as, const 
 // The same product on tm x 128 output tiles (tm = 64 or 128), any K and N that are
 // multiples of 32; whether its 32-bit offsets and LDS hold this shape.
 bool gemm_fp4_tile_supported(bool bwd, int M, int N, int K, int R, bool out_f32);
+// LDS ring slots of a workgroup, and whether two workgroups share a CU.
+struct TileSlots { bool two_per_cu; int ns; };
+TileSlots gemm_fp4_tile_slots(int tm, long tiles, int KR);
 hipError_t launch_gemm_fp4_tile(bool bwd, int tm, const uint8_t* a, const uint8_t* as, const uint8_t* wq,
                                 const uint8_t* ws, int M, int N, int K, const float* P, int R, const uint16_t* lr,
                                 const uint16_t* bias, void* out, bool out_f32, const uint16_t* z, hipStream_t st);
+// Which kernel launch_gemm_fp4 takes: 256 (256x256 tiles), 128 or 64 (that many
+// rows x 128 columns), 0 (register-staged).
+int gemm_fp4_kernel(bool bwd, int M, int N, int K, int R, bool out_f32);
 // Whether the MLP pair's calls take this shape, and the number of projection
 // partials that their workspace holds.
 bool gemm_fp4_fused_supported(bool bwd, int M, int N, int K, int R, int R2);

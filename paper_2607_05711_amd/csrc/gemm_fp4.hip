@@ -14,6 +14,7 @@
 // lane).  Reduction staged 256 elements (128 bytes of codes per row) at a
 // time, double-buffered through LDS with a 16-byte row pad, loads for stage
 // s+1 in flight while stage s runs on the matrix cores.
+#include <climits>
 #include <type_traits>
 
 #include "ft_device.h"
@@ -1026,35 +1027,54 @@ static bool pipe_ok(bool bwd, int M, int N, int K, int R) {
          (size_t)M * (R > 0 ? R : 1) * 4 < (1u << 31) && (size_t)M * NO * 2 < (1u << 31);
 }
 
+// Estimated time of a product on tiles of 256x256, 128x128 and 64x128: rounds
+// of workgroups times the time of one, in units of 10 ns, fitted to
+// back-to-back launches of all three (M = 64 to 18432, KR = 128 to 15872).
+// With few 256x256 tiles most of the chip idles while one CU works through a
+// whole reduction: 512 x 12288 -> 3072 (24 tiles, or 192 of 64x128) 65 us
+// against 31; 512 x 3072 -> 3072 22.5 against 12.3; 2048 x 3072 -> 3072 (96, or
+// 384 of 128x128) 23.4 against 20.4.  With a round of them or more the larger
+// tile's fewer LDS and L2 bytes per MFMA win: 4608 x 3072 -> 9216 83 us against
+// 105 (128x128) and 136 (64x128).
+struct GemmCost { long c256, c128, c64; };
+static GemmCost gemm_cost(int M, int NO, int KR, int R) {
+  const long nst = (KR + 255) / 256, nlr = (R + 31) / 32;
+  auto tiles = [&](int h, int w) { return (long)((M + h - 1) / h) * ((NO + w - 1) / w); };
+  auto rounds = [](long t, long per) { return (t + per - 1) / per; };
+  // Small tiles run two to a CU only while their scales leave room for it: at
+  // 128x128 up to reductions of some 3500, beyond which 1252 x 8448 -> 5376
+  // (420 tiles, two rounds) takes 67 us against 49 on 256x256 tiles.
+  auto small = [&](int tm, long two, long one, long fixed, long lr2, long lr1) {
+    const long t = tiles(tm, 128);
+    const TileSlots sl = gemm_fp4_tile_slots(tm, t, KR);
+    return sl.two_per_cu ? rounds(t, 512) * (fixed + two * nst + lr2 * nlr) : rounds(t, 256) * (fixed + one * nst + lr1 * nlr);
+  };
+  const int ns128 = gemm_fp4_tile_slots(128, 1, KR).ns;
+  const long c256 = rounds(tiles(256, 256), 256) * (850 + 118 * nst + 70 * nlr);
+  const long c64 = small(64, 75, 46, 540, 70, 50);
+  return GemmCost{c256, ns128 < 2 ? LONG_MAX : small(128, 108, ns128 >= 4 ? 68 : 87, 620, 70, 70), c64};
+}
+
+// Which kernel takes a product: 256 (256x256 tiles, k_gemm_fp4_pipe), 128 or 64
+// (tiles of that many rows x 128 columns, k_gemm_fp4_tile), 0 (k_gemm_fp4_generic).
+int gemm_fp4_kernel(bool bwd, int M, int N, int K, int R, bool out_f32) {
+  const bool pipe = pipe_ok(bwd, M, N, K, R);
+  if (!gemm_fp4_tile_supported(bwd, M, N, K, R, out_f32)) return pipe ? 256 : 0;
+  const GemmCost c = gemm_cost(M, bwd ? K : N, bwd ? N : K, R);
+  if (pipe && c.c256 <= std::min(c.c64, c.c128)) return 256;
+  return c.c64 <= c.c128 ? 64 : 128;
+}
+
 hipError_t launch_gemm_fp4(bool bwd, const uint8_t* a, const uint8_t* as, const uint8_t* wq, const uint8_t* ws,
                            int M, int N, int K, const float* P, int R, const uint16_t* lr,
                            const uint16_t* bias, void* out, bool out_f32, const uint16_t* z, hipStream_t st) {
   const int NO = bwd ? K : N;
   const int KR = bwd ? N : K;
   const int tm = (M + GB - 1) / GB, tn = (NO + GB - 1) / GB;
-  const bool pipe = pipe_ok(bwd, M, N, K, R);
-  if (gemm_fp4_tile_supported(bwd, M, N, K, R, out_f32)) {
-    // 256x256 tiles against tiles of 64x128 or 128x128, by estimated time:
-    // rounds of workgroups times the time of one workgroup, in units of 10 ns,
-    // fitted to back-to-back launches of all three (M = 100 to 4608, KR = 256
-    // to 12288).  With few 256x256 tiles most of the chip idles while one CU
-    // works through a whole reduction: 512 x 12288 -> 3072 (24 tiles, or 192
-    // of 64x128) 65 us against 31; 512 x 3072 -> 3072 22.5 against 12.3;
-    // 2048 x 3072 -> 3072 (96, or 384 of 128x128) 23.4 against 20.4.  With a
-    // round of them or more the larger tile's fewer LDS and L2 bytes per MFMA
-    // win: 4608 x 3072 -> 9216 83 us against 105 (128x128) and 136 (64x128).
-    const long nst = (KR + 255) / 256, nlr = (R + 31) / 32;
-    auto tiles = [&](int h, int w) { return (long)((M + h - 1) / h) * ((NO + w - 1) / w); };
-    auto rounds = [](long t, long per) { return (t + per - 1) / per; };
-    const long t64 = tiles(64, 128), t128 = tiles(128, 128);
-    const long c256 = rounds(tiles(256, 256), 256) * (850 + 118 * nst + 70 * nlr);
-    const long c64 = t64 <= 256 ? 540 + 46 * nst + 50 * nlr : rounds(t64, 512) * (540 + 75 * nst + 70 * nlr);
-    const long c128 = t128 <= 256 ? 620 + (nst > 28 ? 87 : 68) * nst + 70 * nlr
-                                  : rounds(t128, 512) * (620 + 108 * nst + 70 * nlr);
-    if (!pipe || std::min(c64, c128) < c256)
-      return launch_gemm_fp4_tile(bwd, c64 <= c128 ? 64 : 128, a, as, wq, ws, M, N, K, P, R, lr, bias, out, out_f32, z, st);
-  }
-  if (pipe) {
+  const int kernel = gemm_fp4_kernel(bwd, M, N, K, R, out_f32);
+  if (kernel == 64 || kernel == 128)
+    return launch_gemm_fp4_tile(bwd, kernel, a, as, wq, ws, M, N, K, P, R, lr, bias, out, out_f32, z, st);
+  if (kernel == 256) {
     const unsigned grid = (unsigned)(tm * tn);
     const uint16_t* b = bwd ? nullptr : bias;
     // A scales in stage pairs when the reduction length is a multiple of 512

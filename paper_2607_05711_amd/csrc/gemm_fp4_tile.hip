@@ -511,18 +511,21 @@ bool gemm_fp4_tile_supported(bool bwd, int M, int N, int K, int R, bool out_f32)
   return slab_bytes(64, KR >> 5, (KR + TK - 1) / TK) + 2 * TileGeom<64>::SLOT <= kCuLds;
 }
 
+// Ring slots: as many as fit, in half of a CU's LDS when there are more
+// workgroups than CUs and it holds two, so that two workgroups share one.
+TileSlots gemm_fp4_tile_slots(int tm, long tiles, int KR) {
+  const int slot = (tm + TN) * TROW, rest = slab_bytes(tm, KR >> 5, (KR + TK - 1) / TK);
+  const int half = tiles > 256 ? (kCuLds / 2 - rest) / slot : 0;
+  return half >= 2 ? TileSlots{true, half} : TileSlots{false, (kCuLds - rest) / slot};
+}
+
 hipError_t launch_gemm_fp4_tile(bool bwd, int tm, const uint8_t* a, const uint8_t* as, const uint8_t* wq,
                                 const uint8_t* ws, int M, int N, int K, const float* P, int R, const uint16_t* lr,
                                 const uint16_t* bias, void* out, bool out_f32, const uint16_t* z, hipStream_t st) {
   const int NO = bwd ? K : N, KR = bwd ? N : K;
-  const int nkb = KR >> 5, nst = (KR + TK - 1) / TK;
-  if (tm == 128 && slab_bytes(128, nkb, nst) + 2 * TileGeom<128>::SLOT > kCuLds) tm = 64;
   const int tiles_m = (M + tm - 1) / tm, tiles_n = (NO + TN - 1) / TN, tiles = tiles_m * tiles_n;
-  const int slot = (tm + TN) * TROW, rest = slab_bytes(tm, nkb, nst);
-  // Slots: as many as fit, in half of a CU's LDS when there are more
-  // workgroups than CUs, so that two share one.
-  int ns = tiles > 256 ? (kCuLds / 2 - rest) / slot : 0;
-  if (ns < 2) ns = (kCuLds - rest) / slot;
+  const int slot = (tm + TN) * TROW, rest = slab_bytes(tm, KR >> 5, (KR + TK - 1) / TK);
+  const int ns = gemm_fp4_tile_slots(tm, tiles, KR).ns;
   const unsigned grid = (unsigned)((tiles + 7) / 8 * 8);
 #define FT_TILE(BW, TM_, NS_) \
   k_gemm_fp4_tile<BW, TM_, NS_><<<grid, 256, (size_t)NS_ * slot + rest, st>>>(a, as, wq, ws, M, N, K, P, R, lr, bias, out, \
