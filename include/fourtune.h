@@ -196,8 +196,9 @@ ft_status ft_linear_bwd_input(const uint8_t *gq, const uint8_t *gs, int64_t M, i
 
 /*
  * MLP pair, forward of FC1 fused with FC2's input preparation (Sec. 3.3, MLP
- * fusion: the GELU and FC2's quantization and down-projection share one pass
- * over FC1's output).  The GEMM is ft_linear_fwd's; then
+ * fusion: the GELU and FC2's quantization and down-projection consume FC1's
+ * output tile while it is on chip, or, where small GEMM tiles are the faster
+ * ones, share one pass over it).  The GEMM is ft_linear_fwd's; then
  *   z[m,n]   = bf16(y[m,n])                         saved for the backward
  *   h[m,n]   = bf16(GELU_tanh(z[m,n]))              FC2's input
  *   hq, hs   = 1x32 MXFP4 codes/scales of h (as ft_quantize_blockwise)
@@ -222,8 +223,7 @@ size_t ft_linear_fwd_gelu_workspace_size(int64_t M, int64_t N, int32_t R2);
 
 /*
  * MLP pair, backward-input of FC2 fused with FC1's gradient preparation: the
- * GEMM is ft_linear_bwd_input's (its fp32 result dH is not rounded; GELU' is
- * applied in its epilogue), then
+ * GEMM is ft_linear_bwd_input's (its fp32 result dH is not rounded), then
  *   dz[m,k]  = bf16(dH[m,k] * GELU_tanh'(z[m,k]))   FC1's incoming gradient
  *   dzq, dzs = 1x32 MXFP4 codes/scales of dz
  *   Qp1[m,j] = sum_k dz[m,k] U1[j,k]                 FC1's Qp (fp32)

@@ -210,6 +210,14 @@ ft_status ft_linear_fwd_gelu(const uint8_t* xq, const uint8_t* xs, int64_t M, in
   if (!ft::gemm_fp4_fused_supported(false, (int)M, (int)N, (int)K, R, R2))
     return fail(FT_ERR_UNSUPPORTED, "fused GELU epilogue needs K %% 128 == 0 and operands below 2 GiB");
   FT_TRY(check_workspace(workspace, workspace_bytes, mlp_workspace(M, N, R2)));
+  if (ft::gemm_fp4_fuse_mlp(false, (int)M, (int)N, (int)K, R, R2)) {
+    const bool parts = mlp_workspace(M, N, R2) > 0;
+    const ft::GemmEpilogue ep{(uint16_t*)z, nullptr, (uint16_t*)h, hq, hs, (const uint16_t*)D2, R2,
+                              parts ? (float*)workspace : P2};
+    return hip_status(ft::launch_gemm_fp4_fused(false, xq, xs, wq, ws, (int)M, (int)N, (int)K, P, R, (const uint16_t*)U,
+                                                (const uint16_t*)bias, ep, P2, stream),
+                      "linear fwd gelu");
+  }
   FT_TRY(hip_status(ft::launch_gemm_fp4(false, xq, xs, wq, ws, (int)M, (int)N, (int)K, P, R, (const uint16_t*)U,
                                         (const uint16_t*)bias, z, false, nullptr, stream),
                     "linear fwd gelu"));
@@ -241,6 +249,14 @@ ft_status ft_linear_bwd_input_dgelu(const uint8_t* gq, const uint8_t* gs, int64_
   if (!ft::gemm_fp4_fused_supported(true, (int)M, (int)N, (int)K, R, R1))
     return fail(FT_ERR_UNSUPPORTED, "fused dGELU epilogue needs N and K multiples of 128 and operands below 2 GiB");
   FT_TRY(check_workspace(workspace, workspace_bytes, mlp_workspace(M, K, R1)));
+  if (ft::gemm_fp4_fuse_mlp(true, (int)M, (int)N, (int)K, R, R1)) {
+    const bool parts = mlp_workspace(M, K, R1) > 0;
+    const ft::GemmEpilogue ep{nullptr, (const uint16_t*)z, (uint16_t*)dz, dzq, dzs, (const uint16_t*)U1, R1,
+                              parts ? (float*)workspace : Qp1};
+    return hip_status(ft::launch_gemm_fp4_fused(true, gq, gs, wq, ws, (int)M, (int)N, (int)K, Qp, R, (const uint16_t*)D,
+                                                nullptr, ep, Qp1, stream),
+                      "linear bwd input dgelu");
+  }
   FT_TRY(hip_status(ft::launch_gemm_fp4(true, gq, gs, wq, ws, (int)M, (int)N, (int)K, Qp, R, (const uint16_t*)D,
                                         nullptr, dz, false, (const uint16_t*)z, stream),
                     "linear bwd input dgelu"));
@@ -362,6 +378,10 @@ ft_status ft_linear_bwd_input_nvfp4(const uint8_t* gq, const uint8_t* gs, const 
 // dispatch, not part of the public header.
 int ftx_gemm_kernel(int bwd, int64_t M, int64_t N, int64_t K, int32_t R, int out_f32) {
   return ft::gemm_fp4_kernel(bwd != 0, (int)M, (int)N, (int)K, R, out_f32 != 0);
+}
+// Whether an MLP call runs whole in the GEMM's epilogue.
+int ftx_mlp_fused(int bwd, int64_t M, int64_t N, int64_t K, int32_t R, int32_t R2) {
+  return ft::gemm_fp4_fuse_mlp(bwd != 0, (int)M, (int)N, (int)K, R, R2) ? 1 : 0;
 }
 
 }  // extern "C"

@@ -167,6 +167,28 @@ __device__ __forceinline__ float gelu_tanh_grad(float z) {
   return fmaf(z * fmaf(kGeluG3, t, kGeluG1) * (1.0f - r), r, r);
 }
 
+// Quantize 8 consecutive bf16 (packed in w) of a 32-element block held by a
+// lane quad: the block absmax is reduced across the quad with DPP.  Returns
+// the 8 E2M1 codes (element 0 in the low nibble) and the block's E8M0 code.
+__device__ __forceinline__ uint32_t quad_quantize8(const uint32_t (&w)[4], uint32_t& scale_code) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int e = 0; e < 4; e++) {
+    const uint32_t a = w[e] & 0x7FFF7FFFu;
+    m = max(m, max(a & 0xFFFFu, a >> 16));
+  }
+  m = max(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0xB1, 0xF, 0xF, true));  // quad_perm [1,0,3,2]
+  m = max(m, (uint32_t)__builtin_amdgcn_mov_dpp((int)m, 0x4E, 0xF, 0xF, true));  // quad_perm [2,3,0,1]
+  scale_code = e8m0_from_amax_bits(m);
+  const float s = e8m0_to_f32(scale_code);
+  uint32_t o = 0;
+  o = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(o, __builtin_bit_cast(v2bf, w[0]), s, 0);
+  o = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(o, __builtin_bit_cast(v2bf, w[1]), s, 1);
+  o = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(o, __builtin_bit_cast(v2bf, w[2]), s, 2);
+  o = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(o, __builtin_bit_cast(v2bf, w[3]), s, 3);
+  return o;
+}
+
 __device__ __forceinline__ v4s lds_read_tr16(const FT_LDS void* p) {
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16((FT_LDS v4s*)p);
 }
@@ -217,7 +239,7 @@ __device__ __forceinline__ int swz128(int r) { return (r & 7) ^ ((r >> 3) & 1); 
 constexpr uint32_t kOobOffset = 0x80000000u;
 
 // Cache policy of buffer stores whose data no kernel reads soon (GEMM outputs,
-// and the MLP pair's dz): non-temporal, so they stream to
+// the MLP epilogues' activations): non-temporal, so they stream to
 // HBM without displacing operand lines from L2.
 constexpr int kStoreNT = 2;
 

@@ -44,7 +44,7 @@ hipError_t launch_reduce_parts(const float* ws, int nparts, size_t n0, float* ou
 // FP4 GEMM.  bwd = false: out[M, N] = A[M, K] . W[N, K]^T  (+ P . U + bias)
 //            bwd = true : out[M, K] = A[M, N] . W[N, K]    (+ P . D^T)
 // z (bwd, bf16 out; NULL for none): out = bf16(that result * GELU'(z)), z bf16
-// [M, K]; needs gemm_fp4_fused_supported.
+// [M, K]; on small tiles only (no gemm_fp4_fuse_mlp).
 hipError_t launch_gemm_fp4(bool bwd, const uint8_t* a, const uint8_t* as, const uint8_t* wq, const uint8_t* ws,
                            int M, int N, int K, const float* P, int R, const uint16_t* lr,
                            const uint16_t* bias, void* out, bool out_f32, const uint16_t* z, hipStream_t st);
@@ -60,6 +60,25 @@ hipError_t launch_gemm_fp4_tile(bool bwd, int tm, const uint8_t* a, const uint8_
 // Which kernel launch_gemm_fp4 takes: 256 (256x256 tiles), 128 or 64 (that many
 // rows x 128 columns), 0 (register-staged).
 int gemm_fp4_kernel(bool bwd, int M, int N, int K, int R, bool out_f32);
+
+// Epilogues of the 256x256 kernel; GELU and DGELU finish the MLP pair's call
+// (the output NO columns feed the next linear).
+enum { EPI_PLAIN = 0, EPI_GELU = 1, EPI_DGELU = 2 };
+struct GemmEpilogue {
+  uint16_t* z_out;        // EPI_GELU: z = bf16(acc) [M, NO]
+  const uint16_t* z_in;   // EPI_DGELU: z saved by the forward [M, NO]
+  uint16_t* y;            // EPI_GELU: h = bf16(GELU(z));  EPI_DGELU: dz = bf16(acc GELU'(z))  [M, NO]
+  uint8_t* q;             // E2M1 codes of y [M, NO/2]
+  uint8_t* s;             // E8M0 scales of y [M, NO/32]
+  const uint16_t* proj;   // EPI_GELU: D2 [NO, R2];  EPI_DGELU: U1 [R2, NO];  unused when R2 == 0
+  int R2;                 // 0, 16, 32, 48 or 64
+  float* parts;           // fp32 partials [tiles over NO][M][R2], or the projection when one tile spans NO
+};
+// Whether the MLP pair's call runs whole in the GEMM's epilogue.
+bool gemm_fp4_fuse_mlp(bool bwd, int M, int N, int K, int R, int R2);
+hipError_t launch_gemm_fp4_fused(bool bwd, const uint8_t* a, const uint8_t* as, const uint8_t* wq, const uint8_t* ws,
+                                 int M, int N, int K, const float* P, int R, const uint16_t* lr, const uint16_t* bias,
+                                 const GemmEpilogue& ep, float* proj_out, hipStream_t st);
 // Whether the MLP pair's calls take this shape, and the number of projection
 // partials that their workspace holds.
 bool gemm_fp4_fused_supported(bool bwd, int M, int N, int K, int R, int R2);

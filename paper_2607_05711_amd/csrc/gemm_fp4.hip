@@ -275,7 +275,6 @@ constexpr int OFF_SB = 66 * 1024;        // W scales: 4 waves x 256 bytes
 constexpr int LR_COLS = 32;              // up-projection columns per low-rank stage
 
 // Stage kinds, and a compile-time tag for the pipeline bodies.
-enum { EPI_PLAIN = 0, EPI_DGELU = 1 };
 enum { SK_NONE = 0, SK_FP4 = 1, SK_LR = 2 };
 template <int V> struct IC { static constexpr int value = V; };
 
@@ -295,14 +294,13 @@ __device__ __forceinline__ void tile_coords(int bid, int tiles_m, int tiles_n, i
   nt = w / gm;
 }
 
-// EPI_DGELU: out = bf16(result * GELU'(z)), z [M, NO] bf16.
 template <bool BWD, bool OUT_F32, int EPI, bool SAP>
 __global__ __launch_bounds__(256, 1) void k_gemm_fp4_pipe(const uint8_t* __restrict__ A, const uint8_t* __restrict__ As,
                                                           const uint8_t* __restrict__ Wq, const uint8_t* __restrict__ Ws,
                                                           int M, int N, int K, const float* __restrict__ P, int R,
                                                           const uint16_t* __restrict__ LR,
                                                           const uint16_t* __restrict__ bias, void* __restrict__ out,
-                                                          int tiles_m, int tiles_n, const uint16_t* __restrict__ z) {
+                                                          int tiles_m, int tiles_n, GemmEpilogue ep) {
   static_assert(OFF_SAP == NSLOT * SLOT, "pair ring follows the slots");
   __shared__ __attribute__((aligned(16))) uint8_t lds[NSLOT * SLOT + (SAP ? 3 * SAP_SLOT : 0)];
 
@@ -961,60 +959,261 @@ __global__ __launch_bounds__(256, 1) void k_gemm_fp4_pipe(const uint8_t* __restr
       }
     }
   } else {
-    // ---- FC2 backward-input of the MLP pair: dz = bf16(acc * GELU'(z)) with
-    // the fp32 acc (dH) unrounded.  Four passes of 32 rows per wave, staged in
-    // LDS as fp32 and read back as 8-column row segments.  The z segments of
-    // pass i are loaded at the start of pass i - 1, ahead of that pass's
-    // stores, so that waiting for them waits only for the stores of pass i - 2
-    // (loads and stores retire in order); all passes' loads at once made every
-    // CU load its whole z tile in one burst.
-    // Bound by its traffic: all CUs read z and write dz in the same phase, 226
-    // MB beside the product's operands (4608 x 3072 -> 12288: 169 us against
-    // 102 us for the plain product; GELU' from an LDS table of bf16 z, some
-    // seven operations for the eleven here, two of them quarter-rate, gave 3
-    // us).  dz is quantized and projected by the quantize kernel, not
-    // here: doing both here took 199 us and left 48 partials to reduce (10 us);
-    // the pass over dz takes 36 us with its reduction.
-    constexpr int SROW = 128 * 4 + 16;                 // staged row stride (bytes)
-    static_assert(4 * 32 * SROW <= NSLOT * SLOT, "epilogue LDS");
-    uint8_t* stg = lds + wave * (32 * SROW);
-    const __amdgpu_buffer_rsrc_t r_y = make_rsrc(out, (uint32_t)M * NO * 2);
-    const __amdgpu_buffer_rsrc_t r_z = make_rsrc(z, (uint32_t)M * NO * 2);
-    auto seg_off = [&](int i, int it) {
-      const int gr = orow0 + 32 * i + 4 * it + g16, gc = ocol0 + 8 * t16;
-      return gr < M && gc < NO ? ((uint32_t)gr * NO + gc) * 2 : kOobOffset;
-    };
+    // ---- MLP epilogues (Sec. 3.3, MLP fusion): the output feeds the next
+    // linear directly.
+    //   EPI_GELU  (FC1 forward):  z = bf16(acc) (saved), h = bf16(GELU(z)),
+    //                             h quantized in 1x32 blocks, FC2's down-
+    //                             projection partial h . D2 over this tile.
+    //   EPI_DGELU (FC2 backward-input): dz = bf16(acc * GELU'(z)) with the
+    //                             fp32 acc (dH) unrounded, dz quantized, FC1's
+    //                             partial dz . U1^T over this tile.
+    // Four passes of 32 rows per wave; in each the wave stages its rows in LDS
+    // (bf16 z, or fp32 dH), reads them back as 8-column row segments (a lane
+    // quad holds one 32-column block), writes the outputs and the block codes,
+    // puts the bf16 result back in place, and multiplies its 32x128 rows with
+    // the staged projection slice.  The two waves sharing rows add their
+    // partials through LDS; one stores them.
+    constexpr bool G = EPI == EPI_GELU;
+    constexpr int SROW = G ? 128 * 2 + 16 : 128 * 4 + 16;   // staged row stride (bytes)
+    constexpr int STG = 32 * SROW;
+    constexpr int PS1 = 64 + 16;                            // EPI_GELU slice [256 n][R2 <= 64]: halfwords per row
+    constexpr int PS2 = 256 + 8;                            // EPI_DGELU slice [R2 <= 64][256 k]: halfwords per row
+    constexpr int PSLICE = G ? 256 * PS1 * 2 : 64 * PS2 * 2;
+    uint8_t* stg = lds + wave * STG;
+    uint16_t* ps = (uint16_t*)(lds + 4 * STG);
+    // This wave's E8M0 codes (128 rows x 4 blocks) and E2M1 codes (128 rows
+    // x 64 bytes), written out once after the passes.
+    uint8_t* sbuf = lds + 4 * STG + PSLICE + wave * 512;
+    uint8_t* qbuf = lds + 4 * STG + PSLICE + 4 * 512 + wave * (128 * 64);
+    static_assert(4 * STG + PSLICE + 4 * 512 + 4 * 128 * 64 <= NSLOT * SLOT, "epilogue LDS");
+    // After the passes and the code flush, the projection partials of the two
+    // waves that share rows are added through four [128 rows][64] fp32
+    // regions at the start of LDS.
+    const int R2 = ep.R2;
+    const int tn = nt;
+    // The projection slice: rows n0..n0+255 of D2 [NO, R2], or columns
+    // n0..n0+255 of U1 [R2, NO]; zeros outside.  EPI_DGELU has registers to
+    // spare: it issues its slice loads, and the first pass's z loads, before
+    // the barrier that frees the ring, so they overlap the wait for the other
+    // waves.  In EPI_GELU, holding the slice across the barrier would spill,
+    // so each of its loads is written to LDS as it arrives, after the barrier.
+    const __amdgpu_buffer_rsrc_t r_y = make_rsrc(ep.y, (uint32_t)M * NO * 2);
+    const __amdgpu_buffer_rsrc_t r_z = make_rsrc(G ? (const void*)ep.z_out : (const void*)ep.z_in, (uint32_t)M * NO * 2);
+    const __amdgpu_buffer_rsrc_t r_q = make_rsrc(ep.q, (uint32_t)M * (NO / 2));
+    const int g16 = lane >> 4, t16 = lane & 15, jj = t16 >> 2, qq = t16 & 3;
+    const int rt2 = (R2 + 31) >> 5;
+    // EPI_DGELU: the z segments of pass i are loaded at the start of pass
+    // i - 1, ahead of that pass's stores, so that waiting for them waits
+    // only for the stores of pass i - 2 (loads and stores retire in order).
+    // Issuing all passes' loads at once made every CU load its whole z tile
+    // in one burst at the start of the epilogue.
     v4i zpre[2][8];
     auto load_z = [&](int i, v4i (&zd)[8]) {
 #pragma unroll
-      for (int it = 0; it < 8; it++) zd[it] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(r_z, seg_off(i, it), 0, 0));
+      for (int it = 0; it < 8; it++) {
+        const int gr = orow0 + 32 * i + 4 * it + g16, gc = ocol0 + 8 * t16;
+        zd[it] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(
+            r_z, (gr < M && gc < NO) ? ((uint32_t)gr * NO + gc) * 2 : kOobOffset, 0, 0));
+      }
     };
-    load_z(0, zpre[0]);   // behind the other waves' last stage
-    __syncthreads();      // all waves are done with the ring
+    uint4 pv[8];
+    if constexpr (!G) {
+      if (R2 > 0) {
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+          const int sl = tid + 256 * u, rr = sl >> 5, cc = (sl & 31) * 8;
+          pv[u] = make_uint4(0, 0, 0, 0);
+          if (rr < R2 && n0 + cc < NO) pv[u] = *(const uint4*)(ep.proj + (size_t)rr * NO + n0 + cc);
+        }
+      }
+      load_z(0, zpre[0]);
+    }
+    __syncthreads();  // all waves are done with the ring
+    if (R2 > 0) {
+      if constexpr (G) {
+        // all eight loads in flight at once, then the LDS writes (left to
+        // itself the compiler waited for each load before the next); rows and
+        // columns outside read zeros
+        const __amdgpu_buffer_rsrc_t rp = make_rsrc(ep.proj, (uint32_t)NO * R2 * 2);
+        v4i v[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+          const int sl = tid + 256 * u, rr = sl >> 3, cc = (sl & 7) * 8;
+          v[u] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(
+              rp, (n0 + rr < NO && cc < R2) ? ((uint32_t)(n0 + rr) * R2 + cc) * 2 : kOobOffset, 0, 0));
+        }
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+          const int sl = tid + 256 * u;
+          *(v4i*)(ps + (sl >> 3) * PS1 + (sl & 7) * 8) = v[u];
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+          const int sl = tid + 256 * u;
+          *(uint4*)(ps + (sl >> 5) * PS2 + (sl & 31) * 8) = pv[u];
+        }
+      }
+    }
+    __syncthreads();
 #pragma unroll   // acc[i] must be indexed by constants
     for (int i = 0; i < 4; i++) {
-      if (i + 1 < 4) load_z(i + 1, zpre[(i + 1) & 1]);
+      if constexpr (!G) {
+        if (i + 1 < 4) load_z(i + 1, zpre[(i + 1) & 1]);
+      }
+      // 1) stage this pass's 32 rows
 #pragma unroll
       for (int j = 0; j < 4; j++)
 #pragma unroll
-        for (int q = 0; q < 4; q++)
-          *(float4*)(stg + r32 * SROW + (32 * j + 8 * q + 4 * h) * 4) =
-              make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+        for (int q = 0; q < 4; q++) {
+          const int col = 32 * j + 8 * q + 4 * h;
+          if constexpr (G) {
+            const v2f x01 = {acc[i][j][4 * q + 0], acc[i][j][4 * q + 1]};
+            const v2f x23 = {acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+            *(v2i*)(stg + r32 * SROW + col * 2) =
+                v2i{(int)__builtin_bit_cast(uint32_t, __builtin_convertvector(x01, v2bf)),
+                    (int)__builtin_bit_cast(uint32_t, __builtin_convertvector(x23, v2bf))};
+          } else {
+            *(float4*)(stg + r32 * SROW + col * 4) =
+                make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+          }
+        }
       __builtin_amdgcn_s_waitcnt(0xc07f);
+      // 2) row segments: outputs, block codes, bf16 result back in place
 #pragma unroll
       for (int it = 0; it < 8; it++) {
-        const uint8_t* srow = stg + (4 * it + g16) * SROW + t16 * 32;
-        const float4 d0 = *(const float4*)srow, d1 = *(const float4*)(srow + 16);
-        const v4i zb = zpre[i & 1][it];
-        const float dh[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
-        v4i w;
+        const int rl = 4 * it + g16, seg = t16;
+        const int gr = orow0 + 32 * i + rl, gc = ocol0 + 8 * seg;
+        const bool inb = gr < M && gc < NO;
+        const uint32_t off2 = inb ? ((uint32_t)gr * NO + gc) * 2 : kOobOffset;
+        uint8_t* srow = stg + rl * SROW;
+        uint32_t w[4];
+        if constexpr (G) {
+          const v4i zb = *(const v4i*)(srow + seg * 16);
+          __builtin_amdgcn_raw_buffer_store_b128(zb, r_z, off2, 0, kStoreNT);
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
-          const v2f dv = {dh[2 * e] * gelu_tanh_grad(bf16_to_f32((uint32_t)zb[e] & 0xFFFFu)),
-                          dh[2 * e + 1] * gelu_tanh_grad(bf16_to_f32((uint32_t)zb[e] >> 16))};
-          w[e] = (int)__builtin_bit_cast(uint32_t, __builtin_convertvector(dv, v2bf));
+          for (int e = 0; e < 4; e++) {
+            const v2f hv = {gelu_tanh(bf16_to_f32((uint32_t)zb[e] & 0xFFFFu)), gelu_tanh(bf16_to_f32((uint32_t)zb[e] >> 16))};
+            w[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(hv, v2bf));
+          }
+        } else {
+          const float4 d0 = *(const float4*)(srow + seg * 32), d1 = *(const float4*)(srow + seg * 32 + 16);
+          const v4i zb = zpre[i & 1][it];
+          const float dh[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            const v2f dv = {dh[2 * e] * gelu_tanh_grad(bf16_to_f32((uint32_t)zb[e] & 0xFFFFu)),
+                            dh[2 * e + 1] * gelu_tanh_grad(bf16_to_f32((uint32_t)zb[e] >> 16))};
+            w[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(dv, v2bf));
+          }
         }
-        __builtin_amdgcn_raw_buffer_store_b128(w, r_y, seg_off(i, it), 0, kStoreNT);
+        const v4i wv = {(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+        __builtin_amdgcn_raw_buffer_store_b128(wv, r_y, off2, 0, kStoreNT);
+        *(v4i*)(srow + seg * 16) = wv;   // bf16 result in place (for the projection)
+        uint32_t sc;
+        const uint32_t codes = quad_quantize8(w, sc);
+        *(uint32_t*)(qbuf + (32 * i + rl) * 64 + seg * 4) = codes;
+        sbuf[(32 * i + rl) * 4 + (seg >> 2)] = (uint8_t)sc;   // the quad's four lanes write the same code
+      }
+      if (R2 == 0) continue;
+      __builtin_amdgcn_s_waitcnt(0xc07f);
+      // 3) projection of the pass's 32 rows over this wave's 128 columns, into
+      //    the pass's first two accumulator tiles (read out in step 1)
+      //    Both 32-column slice tiles are always used (the slice holds zeros
+      //    past R2), and the fragments of k-step ks + 1 are read while the
+      //    MFMAs of k-step ks run.
+      acc[i][0] = v16f{};
+      acc[i][1] = v16f{};
+      auto frag = [&](int ks, v8bf& a, v8bf (&b)[2]) {
+        a = __builtin_bit_cast(v8bf, *(const v4i*)(stg + r32 * SROW + (16 * ks + 8 * h) * 2));
+        const int kloc = wn * 128 + 16 * ks + 8 * h;      // column within the workgroup's 256
+#pragma unroll
+        for (int t = 0; t < 2; t++) {
+          if constexpr (G) {
+            const uint16_t* base = ps + (kloc + jj) * PS1 + 32 * t + 16 * (g16 & 1) + 4 * qq;
+            b[t] = make_v8bf(lds_read_tr16((const FT_LDS void*)base), lds_read_tr16((const FT_LDS void*)(base + 4 * PS1)));
+          } else {
+            b[t] = __builtin_bit_cast(v8bf, *(const v4i*)(ps + (32 * t + r32) * PS2 + kloc));
+          }
+        }
+      };
+      v8bf fa[2], fb[2][2];
+      frag(0, fa[0], fb[0]);
+#pragma unroll
+      for (int ks = 0; ks < 8; ks++) {
+        if (ks + 1 < 8) frag(ks + 1, fa[(ks + 1) & 1], fb[(ks + 1) & 1]);
+#pragma unroll
+        for (int t = 0; t < 2; t++) acc[i][t] = mfma_bf16_32x32x16(fa[ks & 1], fb[ks & 1][t], acc[i][t]);
+      }
+    }
+    // E2M1 codes: 16 bytes (32 columns) of a row per lane, all reads first,
+    // then branch-free stores (outside rows and columns dropped).  The next
+    // product reads the codes at once, so they stay in the caches (MLP pair at
+    // 4608 x 3072 -> 12288: 670 us with non-temporal stores of them, 652 without).
+    {
+      v4i cq[8];
+#pragma unroll
+      for (int q = 0; q < 8; q++) cq[q] = *(const v4i*)(qbuf + (16 * q + (lane >> 2)) * 64 + 16 * (lane & 3));
+#pragma unroll
+      for (int q = 0; q < 8; q++) {
+        const int gr = orow0 + 16 * q + (lane >> 2), c = lane & 3;
+        __builtin_amdgcn_raw_buffer_store_b128(
+            cq[q], r_q, (gr < M && ocol0 + 32 * c < NO) ? (uint32_t)gr * (NO / 2) + (ocol0 / 2) + 16 * c : kOobOffset, 0, 0);
+      }
+    }
+    // E8M0 codes: each lane writes rows lane and lane + 64 of the wave's 128,
+    // four blocks (one dword) per row when aligned and inside the matrix
+    const bool s_al = ((NO >> 5) & 3) == 0 && ocol0 + 128 <= NO;
+#pragma unroll
+    for (int k = 0; k < 2; k++) {
+      const int rr = lane + 64 * k, gr = orow0 + rr;
+      const uint32_t v = *(const uint32_t*)(sbuf + rr * 4);
+      if (gr < M) {
+        uint8_t* d = ep.s + (size_t)gr * (NO >> 5) + (ocol0 >> 5);
+        if (s_al) {
+          *(uint32_t*)d = v;
+        } else {
+#pragma unroll
+          for (int b = 0; b < 4; b++)
+            if (ocol0 + 32 * b < NO) d[b] = (uint8_t)(v >> (8 * b));
+        }
+      }
+    }
+    if (R2 > 0) {
+      // 4) the two waves with the same rows (wn = 0, 1) add their partials,
+      //    all passes at once: each wave stores its own in a 32 KB region
+      //    (the code buffers are flushed, so all of LDS is free), and after
+      //    one barrier each wave adds the two partials of half of its rows
+      //    and stores the sums as 16-byte segments
+      static_assert(4 * 128 * 64 * 4 <= NSLOT * SLOT, "combine regions");
+      __syncthreads();   // every wave is done with the passes' LDS and its code buffers
+      float* mine = (float*)lds + (2 * wn + wm) * (128 * 64);
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int t = 0; t < 2; t++)
+#pragma unroll
+          for (int v = 0; v < 16; v++)
+            mine[(32 * i + 8 * (v >> 2) + 4 * h + (v & 3)) * 64 + 32 * t + r32] = acc[i][t][v];
+      __syncthreads();
+      // all reads first, then branch-free stores (rows past M and columns
+      // past R2 go to an offset past the buffer, which drops them)
+      const float* c0 = (const float*)lds + wm * (128 * 64);          // the wn = 0 partial
+      const float* c1 = (const float*)lds + (2 + wm) * (128 * 64);    // the wn = 1 partial
+      float* dst = tiles_n > 1 ? ep.parts + (size_t)tn * M * R2 : ep.parts;
+      const __amdgpu_buffer_rsrc_t rdst = make_rsrc(dst, (uint32_t)M * R2 * 4);
+      const int j = 4 * (lane & 15);
+      v4f sum[16];
+#pragma unroll
+      for (int q = 0; q < 16; q++) {
+        const int rr = 64 * wn + 4 * q + (lane >> 4);
+        sum[q] = *(const v4f*)(c1 + rr * 64 + j) + *(const v4f*)(c0 + rr * 64 + j);
+      }
+#pragma unroll
+      for (int q = 0; q < 16; q++) {
+        const int gr = orow0 + 64 * wn + 4 * q + (lane >> 4);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, sum[q]), rdst,
+                                               (j < R2 && gr < M) ? ((uint32_t)gr * R2 + j) * 4 : kOobOffset, 0, 0);
       }
     }
   }
@@ -1074,25 +1273,24 @@ hipError_t launch_gemm_fp4(bool bwd, const uint8_t* a, const uint8_t* as, const 
   const int kernel = gemm_fp4_kernel(bwd, M, N, K, R, out_f32);
   if (kernel == 64 || kernel == 128)
     return launch_gemm_fp4_tile(bwd, kernel, a, as, wq, ws, M, N, K, P, R, lr, bias, out, out_f32, z, st);
+  if (z) return hipErrorInvalidValue;   // only small tiles take it: gemm_fp4_fuse_mlp
   if (kernel == 256) {
     const unsigned grid = (unsigned)(tm * tn);
     const uint16_t* b = bwd ? nullptr : bias;
+    const GemmEpilogue none{};
     // A scales in stage pairs when the reduction length is a multiple of 512
-#define FT_PIPE(BW, F32, EP, SP) \
-  k_gemm_fp4_pipe<BW, F32, EP, SP><<<grid, 256, 0, st>>>(a, as, wq, ws, M, N, K, P, R, lr, b, out, tm, tn, z)
+#define FT_PIPE(BW, F32, SP) \
+  k_gemm_fp4_pipe<BW, F32, EPI_PLAIN, SP><<<grid, 256, 0, st>>>(a, as, wq, ws, M, N, K, P, R, lr, b, out, tm, tn, none)
     if (KR % 512 == 0) {
-      if (z) FT_PIPE(true, false, EPI_DGELU, true);
-      else if (!bwd) { if (out_f32) FT_PIPE(false, true, EPI_PLAIN, true); else FT_PIPE(false, false, EPI_PLAIN, true); }
-      else { if (out_f32) FT_PIPE(true, true, EPI_PLAIN, true); else FT_PIPE(true, false, EPI_PLAIN, true); }
+      if (!bwd) { if (out_f32) FT_PIPE(false, true, true); else FT_PIPE(false, false, true); }
+      else { if (out_f32) FT_PIPE(true, true, true); else FT_PIPE(true, false, true); }
     } else {
-      if (z) FT_PIPE(true, false, EPI_DGELU, false);
-      else if (!bwd) { if (out_f32) FT_PIPE(false, true, EPI_PLAIN, false); else FT_PIPE(false, false, EPI_PLAIN, false); }
-      else { if (out_f32) FT_PIPE(true, true, EPI_PLAIN, false); else FT_PIPE(true, false, EPI_PLAIN, false); }
+      if (!bwd) { if (out_f32) FT_PIPE(false, true, false); else FT_PIPE(false, false, false); }
+      else { if (out_f32) FT_PIPE(true, true, false); else FT_PIPE(true, false, false); }
     }
 #undef FT_PIPE
     return hipGetLastError();
   }
-  if (z) return hipErrorInvalidValue;   // callers check gemm_fp4_fused_supported
   dim3 grid(tn, tm);
   if (!bwd) {
     if (out_f32) k_gemm_fp4_generic<false, true><<<grid, 256, 0, st>>>(a, as, wq, ws, M, N, K, P, R, lr, bias, out);
@@ -1104,11 +1302,52 @@ hipError_t launch_gemm_fp4(bool bwd, const uint8_t* a, const uint8_t* as, const 
   return hipGetLastError();
 }
 
+// The MLP pair's calls run whole in the 256x256 kernel's epilogue wherever that
+// kernel takes the product.  Where smaller tiles do, GELU, codes and projection
+// are a pass of their own over z (the dGELU of their epilogue leaves dz, then
+// codes and projection are that pass), and the fused epilogue still wins when
+// the tiles gain less than the pass costs.  In units of 10 ns, fitted to both
+// forms of 36 pairs (M = 128 to 18432, widths to 15360): the pass costs 0.9 us
+// per million elements of z without a projection; with one, 0.45 us less the
+// 1.3 us that the epilogue spends on it; the epilogue's own dGELU, quantization
+// and projection cost 5 us more than the small tile's.  4608 x 3072 -> 12288,
+// forward 145 us fused, 166 apart (no projection), 167 and 174 (R2 = 64),
+// backward 154 and 172, 178 and 184; 2000 x 1024 -> 4096 forward 24 and 30, 33
+// and 33; 512 x 3072 -> 12288 33 and 34, 42 and 39; backward 37 and 33, 46 and 41.
+bool gemm_fp4_fuse_mlp(bool bwd, int M, int N, int K, int R, int R2) {
+  if (gemm_fp4_kernel(bwd, M, N, K, R, false) == 256) return true;
+  if (!pipe_ok(bwd, M, N, K, R)) return false;
+  const int NO = bwd ? K : N;
+  const GemmCost c = gemm_cost(M, NO, bwd ? N : K, R);
+  const double mz = (double)M * NO * 1e-6;
+  const double gain = bwd ? 75 * mz - 500 : R2 == 0 ? 90 * mz : 45 * mz - 130;
+  return (double)(c.c256 - std::min(c.c64, c.c128)) <= gain;
+}
+
 bool gemm_fp4_fused_supported(bool bwd, int M, int N, int K, int R, int R2) {
   return pipe_ok(bwd, M, N, K, R) && R2 >= 0 && R2 <= 64 && R2 % 16 == 0 &&
          (size_t)M * (R2 > 0 ? R2 : 1) * 4 < (1u << 31);
 }
 
 int gemm_fp4_col_tiles(int NO) { return (NO + GB - 1) / GB; }
+
+hipError_t launch_gemm_fp4_fused(bool bwd, const uint8_t* a, const uint8_t* as, const uint8_t* wq, const uint8_t* ws,
+                                 int M, int N, int K, const float* P, int R, const uint16_t* lr, const uint16_t* bias,
+                                 const GemmEpilogue& ep, float* proj_out, hipStream_t st) {
+  const int NO = bwd ? K : N;
+  const int tm = (M + GB - 1) / GB, tn = (NO + GB - 1) / GB;
+  const unsigned grid = (unsigned)(tm * tn);
+  const bool sap = (bwd ? N : K) % 512 == 0;   // A scales in stage pairs
+  if (!bwd) {
+    if (sap) k_gemm_fp4_pipe<false, false, EPI_GELU, true><<<grid, 256, 0, st>>>(a, as, wq, ws, M, N, K, P, R, lr, bias, nullptr, tm, tn, ep);
+    else k_gemm_fp4_pipe<false, false, EPI_GELU, false><<<grid, 256, 0, st>>>(a, as, wq, ws, M, N, K, P, R, lr, bias, nullptr, tm, tn, ep);
+  } else {
+    if (sap) k_gemm_fp4_pipe<true, false, EPI_DGELU, true><<<grid, 256, 0, st>>>(a, as, wq, ws, M, N, K, P, R, lr, nullptr, nullptr, tm, tn, ep);
+    else k_gemm_fp4_pipe<true, false, EPI_DGELU, false><<<grid, 256, 0, st>>>(a, as, wq, ws, M, N, K, P, R, lr, nullptr, nullptr, tm, tn, ep);
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || ep.R2 == 0 || tn == 1) return e;
+  return launch_reduce_parts(ep.parts, tn, (size_t)M * ep.R2, proj_out, 0, nullptr, false, st);
+}
 
 }  // namespace ft

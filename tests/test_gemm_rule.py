@@ -39,3 +39,30 @@ def gemm_kernel(bwd, M, N, K, R=0, out_f32=False):
 ])
 def test_kernel_of_a_product(bwd, M, N, K, R, want):
     assert gemm_kernel(bwd, M, N, K, R) == want
+
+
+def mlp_fused(bwd, M, N, K, R, R2):
+    f = _lib.load().ftx_mlp_fused
+    f.argtypes, f.restype = [ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_int32] * 2, ctypes.c_int
+    return bool(f(int(bwd), M, N, K, R, R2))
+
+
+@pytest.mark.parametrize("bwd,M,D,W,R2,want", [
+    # us in the GEMM's epilogue and as a pass of its own
+    (False, 4608, 3072, 12288, 0, True),    # 145, 166
+    (True, 4608, 3072, 12288, 0, True),     # 154, 172
+    (False, 4608, 3072, 12288, 64, True),   # 167, 174
+    (True, 4608, 3072, 12288, 64, True),    # 178, 184
+    (False, 18432, 3072, 12288, 0, True),   # 529, 683
+    (False, 1500, 2432, 9728, 0, True),     # 36, 51
+    (False, 2000, 1024, 4096, 0, True),     # 24, 30
+    (False, 839, 1920, 7680, 0, True),      # 28, 32
+    (True, 2000, 1024, 4096, 0, False),     # 27, 25
+    (False, 512, 3072, 12288, 64, False),   # 42, 39
+    (True, 512, 3072, 12288, 64, False),    # 46, 41
+    (False, 321, 512, 2048, 0, False),      # 21, 16
+    (True, 321, 512, 2048, 64, False),      # 29, 18
+])
+def test_form_of_the_mlp_calls(bwd, M, D, W, R2, want):
+    N, K = (D, W) if bwd else (W, D)
+    assert mlp_fused(bwd, M, N, K, 64, R2) == want
