@@ -1,12 +1,61 @@
-"""The MLP pair's calls on either side of their rule, with the 256x256 GEMM's
-GELU and dGELU epilogues at the edges of its tiles.  Every case first asserts
-the form that the rule gives it; oracle and bounds are those of the MLP tests."""
+"""The 256x256 FP4 GEMM at the edges of its tiles, and the MLP pair's calls on
+either side of their rule.  Every case first asserts the kernel that the rule
+gives it: ragged rows and columns, a half last stage (reduction an odd multiple
+of 128), paired and unpaired A scales (reduction a multiple of 512 or not), low-
+rank widths with a half last chunk, none and four, both output types, and the
+fused GELU and dGELU epilogues.  Oracle and bounds are those of the parity and
+MLP tests."""
+import numpy as np
 import pytest
+import torch
 
+from oracle import ref
+from paper_2607_05711_amd import _lib, gen
 from tests import test_gpu_mlp as mlp
 from tests.test_gemm_rule import gemm_kernel, mlp_fused
+from tests.test_gpu_parity import check_gemm, dev_bf16, dev_u8, host
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("bwd,M,KR,NO,R", [
+    (False, 1030, 128, 9376, 16),    # one half stage; ragged last row and column tile
+    (False, 1030, 384, 8480, 48),    # a stage and a half; half a last low-rank chunk
+    (False, 1281, 896, 7008, 0),     # one row past a tile; no low-rank stage
+    (False, 1030, 768, 8480, 128),   # whole stages, an odd number of them
+    (False, 1030, 512, 8480, 80),    # paired A scales
+    (False, 1027, 1536, 8224, 64),
+    (True, 1030, 128, 9344, 16),
+    (True, 1030, 384, 8576, 48),
+    (True, 1281, 896, 6784, 0),
+    (True, 1030, 768, 8576, 128),
+    (True, 1030, 512, 8576, 80),
+    (True, 1027, 1536, 8320, 64),
+])
+def test_gemm_on_large_tiles(bwd, M, KR, NO, R):
+    N, K = (KR, NO) if bwd else (NO, KR)
+    assert gemm_kernel(bwd, M, N, K, R, True) == gemm_kernel(bwd, M, N, K, R, False) == 256
+    rng = np.random.default_rng(M + KR + NO + R)
+    aq = rng.integers(0, 256, (M, KR // 2)).astype(np.uint8)
+    asc = rng.integers(110, 140, (M, KR // 32)).astype(np.uint8)
+    wq = rng.integers(0, 256, (N, K // 2)).astype(np.uint8)
+    ws = rng.integers(110, 140, (N // 32, K // 32)).astype(np.uint8)
+    P = LR = Pt = Lt = None
+    if R:
+        P = rng.standard_normal((M, R)).astype(np.float32)
+        LR = gen.f32_to_bf16_bits(rng.standard_normal((K, R) if bwd else (R, N)).astype(np.float32))
+        Pt, Lt = torch.from_numpy(P).to("cuda:0"), dev_bf16(LR)
+        P = P.astype(np.float64)
+    args = (dev_u8(aq), dev_u8(asc), dev_u8(wq), dev_u8(ws), K, Pt, Lt)
+    if bwd:
+        o32, o16 = (_lib.ft_linear_bwd_input(*args, out_dtype=t) for t in (torch.float32, torch.bfloat16))
+        want, S = ref.linear_bwd_input(aq, asc, wq, ws, K, P, LR)
+    else:
+        bias = gen.f32_to_bf16_bits(rng.standard_normal(N).astype(np.float32))
+        o32, o16 = (_lib.ft_linear_fwd(*args, dev_bf16(bias), out_dtype=t) for t in (torch.float32, torch.bfloat16))
+        want, S = ref.linear_fwd(aq, asc, wq, ws, K, P, LR, bias)
+    torch.cuda.synchronize()
+    check_gemm(host(o32), host(o16), want, S, "backward-input" if bwd else "forward")
 
 
 @pytest.mark.parametrize("M,K,N,R,R2,fused", [

@@ -211,9 +211,8 @@ def test_layer_tiny_svd_stabilizer():
 
 @pytest.mark.parametrize("M,K,N,r,rs", [(300, 640, 608, 16, 32), (1, 32, 32, 16, 16), (257, 288, 544, 32, 0),
                                         (64, 512, 256, 0, 0), (520, 1056, 800, 64, 32), (33, 96, 1312, 8, 8),
-                                        # both reductions multiples of 512 (the A scales of two stages load
-                                        # together, the kernels the benchmark times), 3x6 forward and 3x4
-                                        # backward tiles with a ragged last row tile, R = 64 and a bias
+                                        # both reductions multiples of 512, a ragged last row tile, R = 64
+                                        # and a bias
                                         (520, 1024, 1536, 32, 32)])
 def test_layer_ragged(M, K, N, r, rs):
     shape = gen.custom_shape(M, K, N, r=r, r_s=rs, n_outliers=3, outlier_scale=30.0, dy_kind="student_t3")
@@ -334,14 +333,16 @@ def test_gemm_random_codes():
 
 @pytest.mark.parametrize("M,K,N,R", [(300, 640, 384, 48), (129, 128, 128, 16), (257, 1280, 896, 80),
                                      (64, 2304, 640, 0), (520, 1408, 1152, 128), (256, 768, 512, 32),
-                                     # paired A-scale stages in both directions, 2x2 tiles and more, R = 64
+                                     # multiples of 512 in both directions, R = 64
                                      (520, 1024, 1536, 64), (512, 2048, 512, 64)])
 def test_gemm_pipelined_shapes(M, K, N, R):
-    """Reduction lengths that are multiples of 128 run the pipelined kernel:
-    stage counts from one to nine, a half last stage (length an odd multiple
-    of 128) in either direction, low-rank widths with a half last chunk, and
-    row counts that leave partial tiles.  Random code bytes and scales, fp32 P;
-    both output precisions against the oracle."""
+    """Reduction lengths that are multiples of 128, which the pipelined 256x256
+    kernel takes at larger sizes (its own edges: test_gpu_gemm_pipe.py); at
+    these the rule chooses 64x128 tiles.  Stage counts from one to nine, a half
+    last stage (length an odd multiple of 128) in either direction, low-rank
+    widths with a half last chunk, and row counts that leave partial tiles.
+    Random code bytes and scales, fp32 P; both output precisions against the
+    oracle."""
     rng = np.random.default_rng(M + K + N + R)
     xq = rng.integers(0, 256, (M, K // 2)).astype(np.uint8)
     xs = rng.integers(110, 140, (M, K // 32)).astype(np.uint8)
