@@ -182,6 +182,10 @@ ft_status ft_linear_bwd_input(const uint8_t* gq, const uint8_t* gs, int64_t M, i
                     "linear bwd input");
 }
 
+// Products that the GEMM's epilogue adds in a chain into each partial of the
+// MLP projection: the separate pass adds no more.
+constexpr int kMlpChain = 9;
+
 static size_t mlp_workspace(int64_t M, int64_t NO, int32_t R2) {
   if (M <= 0 || NO <= 0 || R2 <= 0 || M > kMaxDim || NO > kMaxDim) return 0;
   const int tiles = ft::gemm_fp4_col_tiles((int)NO);
@@ -222,7 +226,7 @@ ft_status ft_linear_fwd_gelu(const uint8_t* xq, const uint8_t* xs, int64_t M, in
                                         (const uint16_t*)bias, z, false, nullptr, stream),
                     "linear fwd gelu"));
   return hip_status(ft::launch_quant_gelu((const uint16_t*)z, (int)M, (int)N, (uint16_t*)h, hq, hs, (const uint16_t*)D2,
-                                          R2, P2, (float*)workspace, ft::gemm_fp4_col_tiles((int)N), stream),
+                                          R2, P2, (float*)workspace, ft::gemm_fp4_col_tiles((int)N), kMlpChain, stream),
                     "linear fwd gelu (quantize)");
 }
 
@@ -260,8 +264,11 @@ ft_status ft_linear_bwd_input_dgelu(const uint8_t* gq, const uint8_t* gs, int64_
   FT_TRY(hip_status(ft::launch_gemm_fp4(true, gq, gs, wq, ws, (int)M, (int)N, (int)K, Qp, R, (const uint16_t*)D,
                                         nullptr, dz, false, (const uint16_t*)z, stream),
                     "linear bwd input dgelu"));
-  return hip_status(ft::launch_quant_rows((const uint16_t*)dz, (int)M, (int)K, dzq, dzs, (const uint16_t*)U1, R1,
-                                          FT_PROJ_R_BY_COLS, Qp1, (float*)workspace, stream),
+  return hip_status(R1 == 0 ? ft::launch_quant_rows((const uint16_t*)dz, (int)M, (int)K, dzq, dzs, nullptr, 0, 0, nullptr,
+                                                    nullptr, stream)
+                            : ft::launch_quant_proj((const uint16_t*)dz, (int)M, (int)K, dzq, dzs, (const uint16_t*)U1, R1,
+                                                    FT_PROJ_R_BY_COLS, false, Qp1, (float*)workspace,
+                                                    ft::gemm_fp4_col_tiles((int)K), kMlpChain, nullptr, stream),
                     "linear bwd input dgelu (quantize)");
 }
 
@@ -378,6 +385,15 @@ ft_status ft_linear_bwd_input_nvfp4(const uint8_t* gq, const uint8_t* gs, const 
 // dispatch, not part of the public header.
 int ftx_gemm_kernel(int bwd, int64_t M, int64_t N, int64_t K, int32_t R, int out_f32) {
   return ft::gemm_fp4_kernel(bwd != 0, (int)M, (int)N, (int)K, R, out_f32 != 0);
+}
+// Roundings of a projection's sum in the streaming quantize kernel, and in
+// max_groups partials of the chunked kernel.
+void ftx_quant_chain(int64_t rows, int64_t cols, int32_t R, int layout, int32_t* streaming, int32_t* chunked) {
+  int groups, chain;
+  ft::quant_rows_chain((int)rows, (int)cols, R, layout, groups, chain);
+  const int nsteps = (int)((cols + 63) / 64), spg = ft::quant_proj_steps((int)rows, (int)cols, R, groups, chain);
+  *streaming = std::min(spg, nsteps) + 4 + (nsteps + spg - 1) / spg;
+  *chunked = chain + groups;
 }
 // Whether an MLP call runs whole in the GEMM's epilogue.
 int ftx_mlp_fused(int bwd, int64_t M, int64_t N, int64_t K, int32_t R, int32_t R2) {

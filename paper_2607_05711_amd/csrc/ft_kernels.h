@@ -24,16 +24,22 @@ hipError_t launch_quant_rows(const uint16_t* src, int rows, int cols, uint8_t* c
                              const uint16_t* proj, int R, int layout, float* proj_out, float* ws, hipStream_t st,
                              const QuantMode& mode = QuantMode{});
 // h = bf16(GELU(z)) stored and quantized, with the projection h . proj [cols, R]
-// (R = 0: none; R <= 128); ws holds max_groups partials.
+// (R = 0: none; R <= 128); ws holds max_groups partials (max_chain: as below).
 hipError_t launch_quant_gelu(const uint16_t* z, int rows, int cols, uint16_t* h, uint8_t* codes, uint8_t* scales,
-                             const uint16_t* proj, int R, float* proj_out, float* ws, int max_groups, hipStream_t st);
+                             const uint16_t* proj, int R, float* proj_out, float* ws, int max_groups, int max_chain,
+                             hipStream_t st);
 // Streaming form of the row quantization with a projection (nearest-even
-// rounding): at most max_groups partials in ws.  gelu_out: src is z, h =
+// rounding): at most max_groups partials in ws, and no projection sum of more
+// roundings than max_groups partials of max_chain each.  gelu_out: src is z, h =
 // bf16(GELU(z)) is stored there and quantized (layout 0).
+int quant_proj_steps(int rows, int cols, int R, int max_groups, int max_chain);
 bool quant_proj_supported(int rows, int cols, int R);
 hipError_t launch_quant_proj(const uint16_t* src, int rows, int cols, uint8_t* codes, uint8_t* scales,
                              const uint16_t* proj, int R, int layout, bool no_clip, float* proj_out, float* ws,
-                             int max_groups, uint16_t* gelu_out, hipStream_t st);
+                             int max_groups, int max_chain, uint16_t* gelu_out, hipStream_t st);
+// Partials that the row quantization's workspace holds, and the products that
+// the chunked kernel adds into one of them.
+void quant_rows_chain(int rows, int cols, int R, int layout, int& groups, int& chain);
 hipError_t launch_quant_tiles(const uint16_t* src, int rows, int cols, uint8_t* codes, uint8_t* scales,
                               hipStream_t st, const QuantMode& mode = QuantMode{});
 

@@ -1315,9 +1315,9 @@ hipError_t launch_gemm_fp4(bool bwd, const uint8_t* a, const uint8_t* as, const 
 // backward 154 and 172, 178 and 184; 2000 x 1024 -> 4096 forward 24 and 30, 33
 // and 33; 512 x 3072 -> 12288 33 and 34, 42 and 39; backward 37 and 33, 46 and 41.
 bool gemm_fp4_fuse_mlp(bool bwd, int M, int N, int K, int R, int R2) {
-  if (gemm_fp4_kernel(bwd, M, N, K, R, false) == 256) return true;
-  if (!pipe_ok(bwd, M, N, K, R)) return false;
   const int NO = bwd ? K : N;
+  if (gemm_fp4_kernel(bwd, M, N, K, R, false) == 256 || (R2 > 0 && !quant_proj_supported(M, NO, R2))) return true;
+  if (!pipe_ok(bwd, M, N, K, R)) return false;
   const GemmCost c = gemm_cost(M, NO, bwd ? N : K, R);
   const double mz = (double)M * NO * 1e-6;
   const double gain = bwd ? 75 * mz - 500 : R2 == 0 ? 90 * mz : 45 * mz - 130;

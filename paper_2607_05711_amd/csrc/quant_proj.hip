@@ -5,7 +5,8 @@
 //
 // Workgroup: 4 waves over 128 rows x a run of 64-column steps.  A step's rows
 // (each wave its own 32) and its 64 columns of the projection matrix come by
-// buffer loads that write LDS directly, four steps ahead of the one in use,
+// buffer loads that write LDS directly, four steps ahead of the one in use
+// (three for projections wider than 96),
 // so no registers hold data in flight and the loads never wait for
 // arithmetic.  A wave reads its rows from LDS in the MFMA operand layout
 // (lane = row, lanes l and l + 32 sharing one) and quantizes them there: a
@@ -17,12 +18,13 @@
 // the time that its bytes take, so one workgroup with a deep ring per CU is
 // enough (two with three slots each: 39 us against 36 at 4608 x 12288).  The
 // projection's partial sums, one per run, go to the workspace and are added in
-// order by k_reduce_parts.  With that reduction, against the chunked kernel of
-// quantize.hip (nearest-even rounding used it before): 4608 x 12288, R = 64
-// 44.4 -> 35.7 us ([R, cols]) and 43.0 -> 35.5 ([cols, R]); 18432 x 21504,
-// R = 96 278 -> 247; 18432 x 15360 218 -> 189; 8714 x 11648 101 -> 72;
-// 4608 x 9216 and small shapes within 2 %.  With GELU 4608 x 12288 takes 65 us
-// (258 MB; the chunked kernel 82).
+// order by k_reduce_parts.  With that reduction, back to back on one box, against
+// the chunked kernel of quantize.hip (nearest-even rounding used it before):
+// 4608 x 12288, R = 64 44 -> 36 us ([R, cols]) and 43 -> 36 ([cols, R]); 18432 x
+// 21504, R = 96 297 -> 277; 18432 x 15360 227 -> 202; 18432 x 3072, R = 64 43 -> 39;
+// 512 x 3072 12.0 -> 10.2; 4608 x 9216 28 either way; of 71 sizes in both layouts
+// none more than 4 % slower.  With GELU, the form of the MLP pair's calls on small
+// GEMM tiles, 4608 x 12288 takes 65 us (258 MB; the chunked kernel 82).
 #include "ft_device.h"
 #include "ft_kernels.h"
 
@@ -41,7 +43,7 @@ struct QpGeom {
   static constexpr int SLOT = QP_X + PROJ;
   static constexpr int NS = RT == 4 ? 4 : 5;      // ring slots
   // Accumulator sets: a step's four products go round them, so that a sum's
-  // fp32 chain is no longer than the chunked kernel's, whose runs are shorter.
+  // fp32 chain is one product a step long (quant_proj_steps bounds it).
   static constexpr int SETS = 4;
   static constexpr int LOADS = 4 + RT;            // per wave and step
 };
@@ -246,14 +248,21 @@ bool quant_proj_supported(int rows, int cols, int R) {
 // time in steps: rounds of workgroups (one per CU) times a run's steps and the
 // four that its start and end cost, and what each partial adds in traffic
 // (written and read, 4 R bytes a row, where a step of a round moves 20 KB per CU).
-static int qp_steps(int rows, int cols, int R, int max_groups) {
+// A projection's sum rounds once per step, where the sets meet (their three sums
+// weigh as much as four products of a chain) and once per partial; that chain
+// stays within max_chain + max_groups, so that long rows over many row blocks,
+// which fill the chip without partials, still have some.  32768 x 21504, R = 96,
+// [R, cols]: one run of 336 steps takes 446 us with an error of 4.6e-7 (2-norm),
+// the bound 466 us and 2.6e-7, the chunked kernel took 533 us and 2.8e-7.
+int quant_proj_steps(int rows, int cols, int R, int max_groups, int max_chain) {
   const int nsteps = (cols + 63) / 64;
   const long rb = (rows + QP_ROWS - 1) / QP_ROWS;
-  int best = nsteps;
+  int best = ((nsteps + max_groups - 1) / max_groups + 1) & ~1;
   double best_cost = 1e30;
   for (int g = 1; g <= max_groups && g <= nsteps; g++) {
     const int spg = ((nsteps + g - 1) / g + 1) & ~1;   // even: scale dwords stay whole
     const long groups = (nsteps + spg - 1) / spg;
+    if (std::min(spg, nsteps) + 4 + groups > max_chain + max_groups) continue;
     const double cost = (double)((rb * groups + 255) / 256) * (spg + 4) +
                         (groups > 1 ? (double)groups * rows * R * 8.0 / (256 * 20480.0) : 0.0);
     if (cost < best_cost) { best_cost = cost; best = spg; }
@@ -263,8 +272,9 @@ static int qp_steps(int rows, int cols, int R, int max_groups) {
 
 template <int QM, bool GELU>
 static hipError_t launch_qp(const uint16_t* src, int rows, int cols, uint8_t* codes, uint8_t* scales, const uint16_t* proj,
-                            int R, int layout, float* proj_out, float* ws, int max_groups, uint16_t* h, hipStream_t st) {
-  const int spg = qp_steps(rows, cols, R, max_groups);
+                            int R, int layout, float* proj_out, float* ws, int max_groups, int max_chain, uint16_t* h,
+                            hipStream_t st) {
+  const int spg = quant_proj_steps(rows, cols, R, max_groups, max_chain);
   const int groups = ((cols + 63) / 64 + spg - 1) / spg;
   dim3 grid((rows + QP_ROWS - 1) / QP_ROWS, groups);
   float* parts = groups > 1 ? ws : nullptr;
@@ -294,11 +304,13 @@ static hipError_t launch_qp(const uint16_t* src, int rows, int cols, uint8_t* co
 
 hipError_t launch_quant_proj(const uint16_t* src, int rows, int cols, uint8_t* codes, uint8_t* scales,
                              const uint16_t* proj, int R, int layout, bool no_clip, float* proj_out, float* ws,
-                             int max_groups, uint16_t* gelu_out, hipStream_t st) {
-  if (gelu_out) return launch_qp<0, true>(src, rows, cols, codes, scales, proj, R, 0, proj_out, ws, max_groups, gelu_out, st);
-  if (no_clip)
-    return launch_qp<QM_NOCLIP, false>(src, rows, cols, codes, scales, proj, R, layout, proj_out, ws, max_groups, nullptr, st);
-  return launch_qp<0, false>(src, rows, cols, codes, scales, proj, R, layout, proj_out, ws, max_groups, nullptr, st);
+                             int max_groups, int max_chain, uint16_t* gelu_out, hipStream_t st) {
+#define FT_QPL(QM_, GELU_, LAYOUT_) \
+  launch_qp<QM_, GELU_>(src, rows, cols, codes, scales, proj, R, LAYOUT_, proj_out, ws, max_groups, max_chain, gelu_out, st)
+  if (gelu_out) return FT_QPL(0, true, 0);
+  if (no_clip) return FT_QPL(QM_NOCLIP, false, layout);
+  return FT_QPL(0, false, layout);
+#undef FT_QPL
 }
 
 }  // namespace ft

@@ -587,17 +587,19 @@ static bool quant_full_rows(int rows, int cols, int R, int layout) {
   return layout == 0 && R > 0 && R <= 64 && cols <= 32 * QF_MAX_BLOCKS && wg >= 64 && wg <= 256;
 }
 
-// Workgroups along a row of the chunked kernel: the partials that the
-// workspace holds.
-static int quant_groups(int rows, int cols, int R, int layout) {
+// Workgroups along a row of the chunked kernel (the partials that the
+// workspace holds), and the 16-column products that one adds in a chain.
+void quant_rows_chain(int rows, int cols, int R, int layout, int& groups, int& chain) {
   const int cw = quant_chunk_cols(rows, cols, R, layout);
   const int cpw = quant_chunks_per_wg(rows, cols, cw, layout);
-  return ((cols + cw - 1) / cw + cpw - 1) / cpw;
+  groups = ((cols + cw - 1) / cw + cpw - 1) / cpw;
+  chain = (std::min(cpw * cw, cols) + 15) / 16;
 }
 
 size_t quant_rows_workspace(int rows, int cols, int R, int layout) {
   if (R == 0 || quant_full_rows(rows, cols, R, layout)) return 0;
-  const int groups = quant_groups(rows, cols, R, layout);
+  int groups, chain;
+  quant_rows_chain(rows, cols, R, layout, groups, chain);
   return groups > 1 ? (size_t)groups * rows * R * sizeof(float) : 0;
 }
 
@@ -621,9 +623,10 @@ static hipError_t launch_rows_t(const uint16_t* src, int rows, int cols, uint8_t
 }
 
 hipError_t launch_quant_gelu(const uint16_t* z, int rows, int cols, uint16_t* h, uint8_t* codes, uint8_t* scales,
-                             const uint16_t* proj, int R, float* proj_out, float* ws, int max_groups, hipStream_t st) {
+                             const uint16_t* proj, int R, float* proj_out, float* ws, int max_groups, int max_chain,
+                             hipStream_t st) {
   if (R > 0)
-    return launch_quant_proj(z, rows, cols, codes, scales, proj, R, 0, false, proj_out, ws, max_groups, h, st);
+    return launch_quant_proj(z, rows, cols, codes, scales, proj, R, 0, false, proj_out, ws, max_groups, max_chain, h, st);
   dim3 grid((rows + 127) / 128, (cols + 383) / 384);
   k_quant_rows<1, 0, 4, 384, 0, false, true><<<grid, 256, 0, st>>>(z, rows, cols, codes, scales, nullptr, 0, nullptr,
                                                                   nullptr, SrKey{}, 1, h);
@@ -653,9 +656,12 @@ static hipError_t launch_quant_rows_qm(const uint16_t* src, int rows, int cols, 
   // the workspace was sized for; stochastic rounding, bound by its arithmetic,
   // keeps the eight waves per CU of the chunks.
   if constexpr ((QM & QM_SR) == 0) {
-    if (quant_proj_supported(rows, cols, R))
+    if (quant_proj_supported(rows, cols, R)) {
+      int groups, chain;
+      quant_rows_chain(rows, cols, R, layout, groups, chain);
       return launch_quant_proj(src, rows, cols, codes, scales, proj, R, layout, (QM & QM_NOCLIP) != 0, proj_out, ws,
-                               quant_groups(rows, cols, R, layout), nullptr, st);
+                               groups, chain, nullptr, st);
+    }
   }
 #define FT_ROWS(RT_, MODE_, CW_) \
   launch_rows_t<RT_, MODE_, 8, CW_, QM>(src, rows, cols, codes, scales, proj, R, proj_out, ws, key, st)
