@@ -38,3 +38,27 @@ def test_streaming_quantize_project(rows, cols, R, layout, no_clip):
     assert np.array_equal(host(codes), want[0]) and np.array_equal(host(scales), want[1])
     P, Pabs = ref.proj(x, p, layout)
     assert np.all(np.abs(host(out) - P) <= proj_bound(cols, Pabs))
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+def test_rows_too_wide_for_the_streaming_kernel(layout):
+    """From 2^23 columns on, 128 rows pass its 32-bit offsets and the chunked
+    kernel takes the call: codes and scales are those of the call without a
+    projection, the projection within the bound of its chains (at most 256
+    products in a partial, and one partial per 256 columns or more)."""
+    rows, cols, R = 3, (1 << 23) + 32, 16
+    g = torch.Generator(device="cuda:0").manual_seed(layout)
+    x = torch.randn((rows, cols), generator=g, device="cuda:0").to(torch.bfloat16)
+    p = torch.randn((cols, R) if layout == 0 else (R, cols), generator=g, device="cuda:0").to(torch.bfloat16)
+    codes, scales, out = _lib.ft_quantize_blockwise(x, proj=p, proj_layout=layout)
+    codes0, scales0, _ = _lib.ft_quantize_blockwise(x)
+    torch.cuda.synchronize()
+    assert torch.equal(codes, codes0) and torch.equal(scales, scales0)
+    want, mag = torch.zeros((2, rows, R), dtype=torch.float64, device="cuda:0")
+    for c in range(0, cols, 1 << 20):
+        a = x[:, c:c + (1 << 20)].double()
+        b = (p[c:c + (1 << 20)] if layout == 0 else p[:, c:c + (1 << 20)].T.contiguous()).double()
+        want += a @ b
+        mag += a.abs() @ b.abs()
+    bound = (256 + cols / 256) * 2.0 ** -24 * mag
+    assert bool(((out.double() - want).abs() <= bound).all())
