@@ -201,9 +201,14 @@ def gated_residual(x, gate, y):
 
 
 # --------------------------------------------------------------- q, k, v, GELU
+def _in_reach(rows, stride):
+    """Whether the kernels' 32-bit offsets hold this many rows (and a stage past them) of this stride."""
+    return (rows + 63) * stride * 2 + 256 < 1 << 31
+
+
 def _strided(t):
-    """A [rows, heads, head_dim] gradient the backward kernel can read (unit stride within a head)."""
-    if t.stride(-1) != 1 or t.stride(0) % 8 or t.stride(1) % 8 or t.data_ptr() % 16:
+    """A [rows, heads, head_dim] gradient the backward kernels can read (unit stride within a head)."""
+    if t.stride(-1) != 1 or t.stride(0) % 8 or t.stride(1) % 8 or t.data_ptr() % 16 or not _in_reach(t.shape[0], t.stride(0)):
         t = t.clone(memory_format=torch.contiguous_format)
     return t
 
@@ -300,13 +305,14 @@ def _rows(t):
 
 def _attention_ok(*qkv):
     q = qkv[0]
+    # contiguous gradients are in reach too
     if not (_untraced() and q.is_cuda and q.dim() == 3 and q.numel() and q.shape[2] == 128 and
-            q.shape[0] * q.shape[1] < 1 << 27):
+            q.shape[0] * q.shape[1] < 1 << 27 and _in_reach(q.shape[0], q.shape[1] * 128)):
         return False
     for t in qkv:
         if type(t) is not torch.Tensor or t.dtype != BF or t.device != q.device or t.shape != q.shape or \
                 t.stride(2) != 1 or t.stride(0) % 8 or t.stride(1) % 8 or t.data_ptr() % 16 or \
-                (q.shape[0] + 63) * t.stride(0) * 2 + 256 >= 1 << 31:
+                not _in_reach(q.shape[0], t.stride(0)):
             return False
     return True
 

@@ -187,6 +187,23 @@ def test_attention_of_other_shapes_is_the_library_s():
 
 
 @gpu
+def test_attention_gradient_of_far_rows():
+    """A gradient whose rows lie further apart than the kernels' 32-bit offsets reach; q, k and v whose contiguous
+    gradients would."""
+    q, k, v = (rnd((64, 1, 128), 1 + i).requires_grad_(True) for i in range(3))
+    far = torch.empty((64, 8460000), dtype=BF, device=DEV)[:, :128]
+    far.copy_(rnd((64, 128), 4))
+    o = ops.attention(q, k, v)
+    assert type(o.grad_fn).__name__ == "_AttentionBackward"
+    got = torch.autograd.grad(o, (q, k, v), far, retain_graph=True)
+    want = torch.autograd.grad(o, (q, k, v), far.contiguous())
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+    del far
+    big = torch.empty((64, 131072, 128), dtype=BF, device=DEV).transpose(0, 1)
+    assert not ops._attention_ok(big, big, big)
+
+
+@gpu
 def test_calls_that_stay_torch_operations():
     """Gradients of the modulation, other types and layouts, widths past the
     kernel's, functional transforms and a differentiated backward."""
