@@ -305,9 +305,10 @@ def _rows(t):
 
 def _attention_ok(*qkv):
     q = qkv[0]
-    # contiguous gradients are in reach too
+    # contiguous gradients are in reach too; autocast to another type would convert q, k and v
     if not (_untraced() and q.is_cuda and q.dim() == 3 and q.numel() and q.shape[2] == 128 and
-            q.shape[0] * q.shape[1] < 1 << 27 and _in_reach(q.shape[0], q.shape[1] * 128)):
+            q.shape[0] * q.shape[1] < 1 << 27 and _in_reach(q.shape[0], q.shape[1] * 128) and
+            not (torch.is_autocast_enabled("cuda") and torch.get_autocast_dtype("cuda") is not BF)):
         return False
     for t in qkv:
         if type(t) is not torch.Tensor or t.dtype != BF or t.device != q.device or t.shape != q.shape or \

@@ -187,6 +187,18 @@ def test_attention_of_other_shapes_is_the_library_s():
 
 
 @gpu
+def test_attention_under_autocast_is_the_library_s():
+    """Autocast to another type converts q, k and v; to bf16 it changes nothing."""
+    q, k, v = (rnd((40, 2, 128), 1 + i) for i in range(3))
+    with torch.autocast("cuda", dtype=torch.float16):
+        o = ops.attention(q, k, v)
+        assert o.dtype == torch.float16 and torch.equal(o, ops.torch_attention(q, k, v))
+    want = ops.attention(q, k, v)
+    with torch.autocast("cuda", dtype=BF):
+        assert torch.equal(ops.attention(q, k, v), want)
+
+
+@gpu
 def test_attention_gradient_of_far_rows():
     """A gradient whose rows lie further apart than the kernels' 32-bit offsets reach; q, k and v whose contiguous
     gradients would."""
