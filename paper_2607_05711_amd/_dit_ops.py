@@ -384,6 +384,7 @@ def single_stream_mix(h, qn, kn, cos, sin, heads, hd, hidden, mix=attention):
         q, k, v, c = _QkvGelu.apply(h, qn, kn, cos, sin, heads, hidden)
         if mix is attention and _attention_ok(q, k, v):
             return _Attention.apply(c, q, k, v)
-        return _FillLeft.apply(c, mix(q, k, v))
+        o = mix(q, k, v)
+        return _FillLeft.apply(c, o) if o.dtype == BF else torch.cat([o, c[:, hidden:]], -1)
     q, k, v, m = torch_qkv_gelu(h, qn, kn, cos, sin, heads, hd, hidden)
     return torch.cat([mix(q, k, v), m], -1)

@@ -196,6 +196,9 @@ def test_attention_under_autocast_is_the_library_s():
     want = ops.attention(q, k, v)
     with torch.autocast("cuda", dtype=BF):
         assert torch.equal(ops.attention(q, k, v), want)
+    h, n, (cos, sin) = rnd((40, 3 * 256 + 64), 4), torch.ones(128, dtype=BF, device=DEV), tables(40, 128)
+    with torch.autocast("cuda", dtype=torch.float16):      # the MLP part stays bf16: the two meet in fp32
+        assert ops.single_stream_mix(h, n, n, cos, sin, 2, 128, 256).dtype == torch.float32
 
 
 @gpu
