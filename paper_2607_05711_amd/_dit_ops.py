@@ -31,20 +31,26 @@ _SIGNATURES = {
 _ready = None
 
 
-def _call(name, dev, *args):
+def _load():
     global _ready
     if _ready is None:
         L = _lib.load()
         for n, sig in _SIGNATURES.items():
             getattr(L, n).argtypes = sig
             getattr(L, n).restype = ctypes.c_int
+        L.ftdit_mod_parts.argtypes, L.ftdit_mod_parts.restype = [_I, _I], _I
         _ready = L
+    return _ready
+
+
+def _call(name, dev, *args):
+    f = getattr(_load(), name)
     args = [a.data_ptr() if isinstance(a, torch.Tensor) else a for a in args]
     if torch.cuda.current_device() != dev.index:
         with torch.cuda.device(dev):
-            status = getattr(_ready, name)(*args, torch.cuda.current_stream(dev).cuda_stream)
+            status = f(*args, _lib._stream(dev))
     else:
-        status = getattr(_ready, name)(*args, torch.cuda.current_stream(dev).cuda_stream)
+        status = f(*args, _lib._stream(dev))
     if status != _lib.FT_OK:
         raise _lib.FourTuneError(status, name)
 
@@ -149,12 +155,6 @@ def modulate(x, shift, scale):
 
 
 # ----------------------------------------------------------- modulation vector
-def _mod_parts(K, N):
-    f = _lib.load().ftdit_mod_parts
-    f.argtypes, f.restype = [_I, _I], _I
-    return f(K, N)
-
-
 def modulation(vec, w):
     """silu(vec) @ w: the block's shift, scale and gate vectors."""
     if vec.is_cuda and _untraced() and vec.dim() > 0 and w.dim() == 2 and 0 < vec.numel() == vec.shape[-1] == w.shape[0] < 1 << 20 and \
@@ -162,41 +162,40 @@ def modulation(vec, w):
             not torch.is_autocast_enabled("cuda"):
         out = torch.empty(vec.shape[:-1] + w.shape[1:], dtype=BF, device=vec.device)
         K, N = w.shape
-        parts = torch.empty((_mod_parts(K, N), N), dtype=torch.float32, device=vec.device)
+        parts = torch.empty((_load().ftdit_mod_parts(K, N), N), dtype=torch.float32, device=vec.device)
         _call("ftdit_mod", vec.device, vec, w, out, parts, K, N)
         return out
     return F.silu(vec) @ w
 
 
 # ------------------------------------------------------------- gated residual
+def _gate(x, gate, y):
+    out = torch.empty_like(y)
+    H = y.shape[-1]
+    _call("ftdit_gate", y.device, x, gate, y, out, y.numel() // H, H)
+    return out
+
+
 class _Gate(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, gate, y):
-        out = torch.empty_like(x)
-        H = x.shape[-1]
-        _call("ftdit_gate", x.device, x, gate, y, out, x.numel() // H, H)
         ctx.save_for_backward(gate)
-        return out
+        return _gate(x, gate, y)
 
     @staticmethod
     def backward(ctx, dout):
         gate, = ctx.saved_tensors
         if torch.is_grad_enabled():
             return dout, None, dout * gate
-        dy = None
-        if ctx.needs_input_grad[2]:
-            d = _aligned(dout)
-            dy = torch.empty_like(d)
-            H = d.shape[-1]
-            _call("ftdit_gate", d.device, None, gate, d, dy, d.numel() // H, H)
-        return dout, None, dy
+        return dout, None, _gate(None, gate, _aligned(dout)) if ctx.needs_input_grad[2] else None
 
 
 def gated_residual(x, gate, y):
     """x + gate * y, the product rounded to bf16 before the sum."""
     if _untraced() and x.is_cuda and x.numel() and x.shape == y.shape and x.shape[-1] % 8 == 0 and \
             x.shape[-1] < 1 << 24 and _plain(BF, x.device, x, gate, y) and _row(gate, x) and _constant(gate):
-        return _Gate.apply(x, gate, y)
+        # (without gradients an autograd function is 4 us of a small call's time)
+        return _gate(x, gate, y) if _constant(x, y) else _Gate.apply(x, gate, y)
     return x + gate * y
 
 
