@@ -7,7 +7,10 @@
 // Workgroups cover one column chunk, or (MC) a few consecutive ones with
 // the projection slice re-staged between them; their partial projections
 // are summed by k_reduce_parts.  With a projection and nearest-even rounding
-// the streaming kernel of quant_proj.hip takes its place.
+// the streaming kernel of quant_proj.hip takes its place below 2^23 columns.
+// With stochastic rounding the loop over a chunk's steps is not unrolled around
+// the random bits, so its rows in flight (xv) are indexed at run time and lie
+// in scratch memory: 16 bytes x 4 per step and lane.
 // k_quant_rows_fr: the same for a [cols, R] projection with whole rows per
 // workgroup, which adds its partial projections itself.
 // k_quant_tiles: 32x32 tiles of the frozen weight (Sec. 3.2), offline.
@@ -527,13 +530,15 @@ __global__ __launch_bounds__(256) void k_quant_tiles(const uint16_t* __restrict_
 }
 
 // ---------------------------------------------------------------- launchers
-// Geometry per mode, from timing at the FLUX shapes: 8 waves (256 rows) per
-// workgroup amortize the staged projection chunk.  The [cols, R] projection
-// takes 384-column chunks, or 256 when that would leave fewer workgroups
-// than CUs (4608 x 3072: 16.5 us against 17.6); more chunks mean more
-// partial sums, which dominate for long rows.  The [R, cols] projection
-// takes 768-column chunks (fewer partial sums; 384 and 512 are slower)
-// while the chunk fits LDS.
+// Geometry of the chunked kernel, from timing at the FLUX shapes with
+// nearest-even rounding, which the streaming kernel has taken over: 8 waves
+// (256 rows) per workgroup amortize the staged projection chunk.  The [cols, R]
+// projection takes 384-column chunks, or 256 when that would leave fewer
+// workgroups than CUs (4608 x 3072: 16.5 us against 17.6); more chunks mean
+// more partial sums, which dominate for long rows.  The [R, cols] projection
+// takes 768-column chunks (fewer partial sums; 384 and 512 are slower) while
+// the chunk fits LDS.  These rules still size the workspace and so bound the
+// streaming kernel's partials and the length of its sums.
 // Chunks per workgroup of the chunked kernel (256-row workgroups), so that
 // long rows leave fewer partial sums: for [cols, R] as many as 6 while 384
 // workgroups remain (18432 x 15360 at 512 columns: 6 partials per row
@@ -611,12 +616,19 @@ static hipError_t launch_rows_t(const uint16_t* src, int rows, int cols, uint8_t
   const int nch = (cols + CW - 1) / CW;
   dim3 grid((rows + 32 * WAVES - 1) / (32 * WAVES), (nch + cpw - 1) / cpw);
   float* parts = MODE != 0 && grid.y > 1 ? ws : nullptr;
-  if (cpw > 1)
-    k_quant_rows<RT, MODE, WAVES, CW, QM, true><<<grid, 64 * WAVES, 0, st>>>(src, rows, cols, codes, scales, proj, R,
-                                                                           proj_out, parts, key, cpw);
-  else
-    k_quant_rows<RT, MODE, WAVES, CW, QM, false><<<grid, 64 * WAVES, 0, st>>>(src, rows, cols, codes, scales, proj, R,
-                                                                            proj_out, parts, key, 1);
+  // Nearest-even rows with a projection come here from 2^23 columns on: always several chunks.
+  constexpr bool MANY = MODE != 0, ONE = MODE == 0 || (QM & QM_SR) != 0;
+  if (cpw > 1) {
+    if constexpr (MANY)
+      k_quant_rows<RT, MODE, WAVES, CW, QM, true><<<grid, 64 * WAVES, 0, st>>>(src, rows, cols, codes, scales, proj, R,
+                                                                             proj_out, parts, key, cpw);
+  } else {
+    if constexpr (ONE)
+      k_quant_rows<RT, MODE, WAVES, CW, QM, false><<<grid, 64 * WAVES, 0, st>>>(src, rows, cols, codes, scales, proj, R,
+                                                                              proj_out, parts, key, 1);
+    else
+      return hipErrorInvalidValue;
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !parts) return e;
   return launch_reduce_parts(parts, (int)grid.y, (size_t)rows * R, proj_out, 0, nullptr, false, st);
@@ -652,9 +664,9 @@ static hipError_t launch_quant_rows_qm(const uint16_t* src, int rows, int cols, 
     return hipGetLastError();
   }
   // Nearest-even rounding with a projection streams (any size its 32-bit
-  // offsets reach, up to 8 million columns), with at most the partials that
-  // the workspace was sized for; stochastic rounding, bound by its arithmetic,
-  // keeps the eight waves per CU of the chunks.
+  // offsets reach, below 2^23 columns), with at most the partials that the
+  // workspace was sized for; stochastic rounding keeps the chunks, whose eight
+  // waves a CU share its arithmetic.
   if constexpr ((QM & QM_SR) == 0) {
     if (quant_proj_supported(rows, cols, R)) {
       int groups, chain;
@@ -665,11 +677,9 @@ static hipError_t launch_quant_rows_qm(const uint16_t* src, int rows, int cols, 
   }
 #define FT_ROWS(RT_, MODE_, CW_) \
   launch_rows_t<RT_, MODE_, 8, CW_, QM>(src, rows, cols, codes, scales, proj, R, proj_out, ws, key, st)
-  if (layout == 0) {
-    const int cw = quant_chunk_cols(rows, cols, R, layout);
-    if (cw == 640) return rt == 1 ? FT_ROWS(1, 1, 640) : FT_ROWS(2, 1, 640);
-    if (cw == 512) return FT_ROWS(3, 1, 512);
-    if (cw == 256) {
+  const int cw = quant_chunk_cols(rows, cols, R, layout);
+  if constexpr ((QM & QM_SR) != 0) {   // chunks of fewer columns than fit LDS, where those are too few workgroups
+    if (layout == 0 && cw == 256) {
       switch (rt) {
         case 1: return FT_ROWS(1, 1, 256);
         case 2: return FT_ROWS(2, 1, 256);
@@ -677,14 +687,23 @@ static hipError_t launch_quant_rows_qm(const uint16_t* src, int rows, int cols, 
         default: return FT_ROWS(4, 1, 256);
       }
     }
+    if (layout == 0 && cw == 384 && rt < 4) {
+      switch (rt) {
+        case 1: return FT_ROWS(1, 1, 384);
+        case 2: return FT_ROWS(2, 1, 384);
+        default: return FT_ROWS(3, 1, 384);
+      }
+    }
+    if (layout != 0 && cw == 256) return rt == 1 ? FT_ROWS(1, 2, 256) : FT_ROWS(2, 2, 256);
+  }
+  if (layout == 0) {
     switch (rt) {
-      case 1: return FT_ROWS(1, 1, 384);
-      case 2: return FT_ROWS(2, 1, 384);
-      case 3: return FT_ROWS(3, 1, 384);
+      case 1: return FT_ROWS(1, 1, 640);
+      case 2: return FT_ROWS(2, 1, 640);
+      case 3: return FT_ROWS(3, 1, 512);
       default: return FT_ROWS(4, 1, 384);
     }
   }
-  if (quant_chunk_cols(rows, cols, R, layout) == 256) return rt == 1 ? FT_ROWS(1, 2, 256) : FT_ROWS(2, 2, 256);
   switch (rt) {
     case 1: return FT_ROWS(1, 2, 768);
     case 2: return FT_ROWS(2, 2, 768);

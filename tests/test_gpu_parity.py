@@ -98,15 +98,12 @@ def test_quantize_tiles_bitexact(rows, cols):
 @pytest.mark.parametrize("rows,cols,R,layout", [(128, 256, 32, 0), (300, 640, 48, 0), (129, 1184, 64, 0),
                                                 (200, 416, 128, 0), (128, 256, 32, 1), (300, 800, 96, 1),
                                                 (77, 4096, 16, 1), (513, 384, 112, 0),
-                                                # enough workgroups for 384-column chunks
+                                                # many row blocks; a last run of one step, a step and a half
+                                                # and half a step (the workspace rule's chunks of 384, 512 and
+                                                # 640 columns bound the runs of these)
                                                 (8224, 3072, 64, 0),
-                                                # rows longer than 4096: column chunks, ragged last chunk
                                                 (2304, 10976, 64, 0),
-                                                # ... in 640-column chunks (R <= 64) or 512 (R = 96) when
-                                                # those still make 256 workgroups; ragged rows, last chunks
-                                                # of one step, a step and a half, half a step
                                                 (8200, 6464, 64, 0), (8200, 5216, 32, 0), (8200, 5152, 96, 0),
-                                                # ... and for rows of at most 4096 when those fill a round
                                                 (13200, 3136, 64, 0), (11000, 3104, 96, 0),
                                                 # [cols, R] with whole rows per workgroup (64..256 workgroups
                                                 # of 24 rows, or of 32 when 24 would need more than 256; rows
@@ -115,14 +112,11 @@ def test_quantize_tiles_bitexact(rows, cols):
                                                 (2304, 4064, 64, 0), (2200, 1056, 16, 0), (2100, 160, 64, 0),
                                                 (8192, 800, 48, 0), (2080, 96, 32, 0), (1601, 512, 64, 0),
                                                 (7001, 288, 64, 0),
-                                                # [R, cols] at the same row counts (column chunks: 256 columns
-                                                # where 768 would make fewer than 128 workgroups, 512 for
-                                                # R = 96) and with 768-column chunks and a ragged last one
+                                                # [R, cols] at the same row counts, and at the rule's chunks of
+                                                # 256, 512 and 768 columns
                                                 (2065, 4160, 64, 1), (3000, 2080, 32, 1), (2080, 640, 48, 1),
                                                 (1000, 5152, 96, 1), (4352, 6400, 64, 1),
-                                                # workgroups looping over several chunks: ragged rows, a
-                                                # last group of one ragged chunk ([R, cols]: 22 chunks of
-                                                # 768, 3 per group; [cols, R]: 26 of 640, 5 per group)
+                                                # long runs (the rule's groups of several chunks)
                                                 (16640, 16384, 64, 1), (16640, 16384, 64, 0)])
 def test_quantize_fused_projection(rows, cols, R, layout):
     rng = np.random.default_rng(rows + cols + R)
