@@ -749,8 +749,8 @@ def dit_step_timing(torch, dev, seed, steps, warmup, cfg=None):
                        "img_tokens": cfg.img_tokens, "txt_tokens": cfg.txt_tokens, "hidden": cfg.hidden,
                        "heads": cfg.heads, "mlp": cfg.mlp, "lora_rank": cfg.lora_rank,
                        "stabilizer_rank": cfg.stab_rank},
-            "step": "forward, MSE loss, backward, AdamW on every LoRA factor; attention, norms, modulation "
-                    "and RoPE as torch operations (fused attention kernels only)",
+            "step": "forward, MSE loss, backward, AdamW on every LoRA factor; attention, norms, modulation, "
+                    "RoPE and gated residuals on this library's kernels in both models",
             "steps": steps, "warmup": warmup, "data": "synthetic, random weights"}
 
 

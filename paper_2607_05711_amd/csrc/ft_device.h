@@ -122,8 +122,10 @@ struct SrKey { uint32_t k0, k1, s0, s1; };
 //     down (u + 1/2 < 2^17 t is u < X).  2^17 t - 1/2 is exact in fp32 for
 //     2^17 t >= 2^-17; below that it is -1/2 or a little more, and X is 0.
 // With the 64-bit products above, 4608 x 9216 with R = 64 and stochastic
-// rounding takes 82 us instead of 108 (bound by the vector unit: some 136
-// operations here and 20 wide products per 8 elements).
+// rounding takes 82 us instead of 108.  Some 136 operations here and 20 wide
+// products per 8 elements are about 30 us of that on 1024 SIMDs, HBM traffic
+// 22; the rows' way through scratch memory (quantize.hip) and 216 workgroups
+// on 256 CUs are the rest.
 __device__ __forceinline__ uint32_t sr_fp4x8(const uint32_t (&w)[4], uint32_t scale_code, const uint32_t (&rnd)[4]) {
   const float inv = __uint_as_float((254u - scale_code) << 23);   // 2^-e, a normal fp32 for every code <= 253
   uint32_t o = 0;

@@ -527,6 +527,8 @@ hipError_t launch_gemm_fp4_tile(bool bwd, int tm, const uint8_t* a, const uint8_
   const int slot = (tm + TN) * TROW, rest = slab_bytes(tm, KR >> 5, (KR + TK - 1) / TK);
   const int ns = gemm_fp4_tile_slots(tm, tiles, KR).ns;
   const unsigned grid = (unsigned)((tiles + 7) / 8 * 8);
+  // The ring depth is a template argument; depths between the compiled ones
+  // (of 64-row tiles 4, of 128-row tiles 3) use the next smaller.
 #define FT_TILE(BW, TM_, NS_) \
   k_gemm_fp4_tile<BW, TM_, NS_><<<grid, 256, (size_t)NS_ * slot + rest, st>>>(a, as, wq, ws, M, N, K, P, R, lr, bias, out, \
                                                                           out_f32 ? 1 : 0, tiles_m, tiles_n, z)
